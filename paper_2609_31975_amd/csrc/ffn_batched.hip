@@ -1,5 +1,6 @@
-// gfx950 kernels for a batch of 2..64 tokens with bf16 weights (paper Section 5.3: the
-// rows of W_up / W_down are read once for the union of the tokens' active sets).
+// gfx950 kernels for a batch of 2..64 tokens (paper Section 5.3: the rows of W_up / W_down are
+// read once for the union of the tokens' active sets), bf16, int8 / int4 or fp32 weights.  What
+// follows describes bf16; is_f32 says what differs for fp32.
 //
 // Every contraction runs on the matrix cores (v_mfma_f32_16x16x32_bf16): LoPA's A x,
 // the gate (W_gate x, or B z), the W_up dots of the union rows and the down
@@ -18,8 +19,8 @@
 //                  in fragment order, read by the next two kernels;
 //   k_lopa_z_mfma  z = A x as two partial sums over halves of the d range;
 //   k_gate_up_mfma per segment of at most 64 rows: gate, union of the tokens' active rows,
-//                  ascending, W_up dots of the union rows; zval = act * v is left in
-//                  the A-operand fragment order of the down product (k_gate_up_q4 does the
+//                  ascending, W_up dots of the union rows; zval = act * v is left by
+//                  quads of entries for the down product (k_gate_up_q4 does the
 //                  same for 2..4 tokens on 4x4x4 products, k_gate_up_mfma2 at two
 //                  workgroups a CU where d_ff is large);
 //   k_down_mfma    Y[tokens][cols] += Z[tokens][entries] D[entries][cols] over the
@@ -46,10 +47,12 @@ namespace {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef short short4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kTiles = 4;                // 16-row tiles of a gate segment
 constexpr int kSegRowsB = 16 * kTiles;   // rows per gate segment (one 64-lane ballot)
 constexpr int kParts = kBlock / kWave;   // k parts of a workgroup, one per wave
+constexpr int kSegQuads = kSegRowsB / 4; // union entries go to the down kernel by quads
 constexpr int kSegGrid = 256;            // most workgroups of the gate kernel, one per CU
 constexpr int kSegGrid2 = 512;           // the same at two workgroups per CU
 
@@ -57,6 +60,33 @@ __device__ __forceinline__ f32x4_t mfma16(bf16x8_t a, bf16x8_t b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 __device__ __forceinline__ bf16x8_t bf8(uint4 v) { return __builtin_bit_cast(bf16x8_t, v); }
+
+// fp32 weights: the same kernels on v_mfma_f32_16x16x4_f32.  A tile chunk is then 4 fp32 (16
+// bytes, as 8 bf16 are), the tokens, z and zval stay fp32, and a k step of four chunks is four
+// products: component j of every lane's chunk in product j.  A product adds its terms one after
+// the other, so a long range in one accumulator rounds like a serial sum (a call's error against
+// 64 bits at d = 3840, d_ff = 14231, r = 480, 16 tokens: 7.9e-7, the vector-ALU kernels' 3.5e-7).
+// Every k step of the gate and W_up products is summed from zero, then into its load group's
+// sum, then into the running sum; the down product sums every group of 32 rows from zero (3.4e-7).
+template <class W>
+constexpr bool is_f32() {
+  return W::EPC == 4;
+}
+template <class W>
+constexpr int tile_elems() {  // elements of a 16-byte tile chunk
+  return is_f32<W>() ? 4 : 8;
+}
+template <class W>
+constexpr uint32_t tok_bytes() {  // bytes of a token's fp32 chunk
+  return is_f32<W>() ? 16u : 32u;
+}
+__device__ __forceinline__ f32x4_t mfma16f(float a, float b, f32x4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+template <int J>
+__device__ __forceinline__ float comp(const uint4& v) {
+  return __uint_as_float(J == 0 ? v.x : J == 1 ? v.y : J == 2 ? v.z : v.w);
+}
 
 // v = hi + lo with both in bf16 (round to nearest even twice)
 __device__ __forceinline__ void split8(const float (&v)[8], bf16x8_t& hi, bf16x8_t& lo) {
@@ -130,7 +160,7 @@ __device__ __forceinline__ void kpart(int C, int kp, int np, int* ks0, int* ks1)
 // they go to the tile, which keeps the bf16 layout.
 template <int RT, int KU, class W = WBf16>
 struct WStage {
-  static constexpr int R8 = W::EPC / 8;       // tile chunks per loaded chunk
+  static constexpr int R8 = W::EPC / tile_elems<W>();  // tile chunks per loaded chunk
   static constexpr int LPR = 4 * KU / R8;     // lanes per row of a load instruction
   static constexpr int RPI = kWave / LPR;     // rows per load instruction
   static constexpr int NI = (16 * RT + RPI - 1) / RPI;  // load instructions per group
@@ -161,10 +191,11 @@ __device__ __forceinline__ void stage_rows(int* roff, int C, RowOf row_of) {  //
 //  - PRE (pre-split, NP = 1): b[u][nt][0] = the hi and lo fragments of the lane, read from
 //    planes [k step][token tile][lane] of uint4 (k_split_tokens); the lo plane starts
 //    part_bytes after the hi plane; tn = the planes' token-tile count.
+// fp32 weights: one piece instead of two, the chunk's 4 fp32 (one plane when PRE).
 template <int RT, int NT, int KU, int NP, class W = WBf16>
 struct Frags {
   uint4 a[WStage<RT, KU, W>::NI];
-  uint4 b[KU][NT][NP][2];
+  uint4 b[KU][NT][NP][is_f32<W>() ? 1 : 2];
 };
 
 template <int RT, int NT, int KU, int NP, bool PRE = false, class W = WBf16>
@@ -189,7 +220,7 @@ __device__ __forceinline__ void load_frags(Frags<RT, NT, KU, NP, W>& f, const Bu
       for (int nt = 0; nt < NT; ++nt) {
         const uint32_t off = ks + u < ks1 ? 16u * ((uint32_t)((ks + u) * tn + nt) * kWave + lane) : kOOB;
         f.b[u][nt][0][0] = ldb(tb, off);
-        f.b[u][nt][0][1] = ldb(tb, off + part_bytes);
+        if constexpr (!is_f32<W>()) f.b[u][nt][0][1] = ldb(tb, off + part_bytes);
       }
     return;
   }
@@ -201,11 +232,11 @@ __device__ __forceinline__ void load_frags(Frags<RT, NT, KU, NP, W>& f, const Bu
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       const int tok = 16 * nt + m;
-      const uint32_t off = (cv && tok < T) ? 32u * (uint32_t)(tok * C + c) : kOOB;
+      const uint32_t off = (cv && tok < T) ? tok_bytes<W>() * (uint32_t)(tok * C + c) : kOOB;
 #pragma unroll
       for (int p = 0; p < NP; ++p) {
         f.b[u][nt][p][0] = ldb(tb, off + p * part_bytes);
-        f.b[u][nt][p][1] = ldb(tb, off + p * part_bytes + 16);
+        if constexpr (!is_f32<W>()) f.b[u][nt][p][1] = ldb(tb, off + p * part_bytes + 16);
       }
     }
   }
@@ -254,10 +285,41 @@ __device__ __forceinline__ void mma_frags(const Frags<RT, NT, KU, NP, W>& f, uin
     }
   }
   __builtin_amdgcn_wave_barrier();  // LDS operations of a wave complete in order
+  f32x4_t grp[RT][NT];  // fp32 weights: the group's sums
 #pragma unroll
   for (int u = 0; u < KU; ++u)
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
+      if constexpr (is_f32<W>()) {
+        float v[4];
+        v[0] = comp<0>(f.b[u][nt][0][0]);
+        v[1] = comp<1>(f.b[u][nt][0][0]);
+        v[2] = comp<2>(f.b[u][nt][0][0]);
+        v[3] = comp<3>(f.b[u][nt][0][0]);
+#pragma unroll
+        for (int p = 1; p < NP; ++p) {
+          v[0] += comp<0>(f.b[u][nt][p][0]);
+          v[1] += comp<1>(f.b[u][nt][p][0]);
+          v[2] += comp<2>(f.b[u][nt][p][0]);
+          v[3] += comp<3>(f.b[u][nt][p][0]);
+        }
+        uint4 a[RT];
+        f32x4_t ks[RT];  // the k step's sums
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) a[rt] = tile[(16 * rt + m) * S::PITCH + 4 * u + g];
+        // the row tiles inside: no product waits on the one before it
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) ks[rt] = mfma16f(comp<0>(a[rt]), v[0], f32x4_t{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) ks[rt] = mfma16f(comp<1>(a[rt]), v[1], ks[rt]);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) ks[rt] = mfma16f(comp<2>(a[rt]), v[2], ks[rt]);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) ks[rt] = mfma16f(comp<3>(a[rt]), v[3], ks[rt]);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) grp[rt][nt] = u == 0 ? ks[rt] : grp[rt][nt] + ks[rt];
+        continue;
+      } else {
       bf16x8_t hi, lo;
       if constexpr (PRE) {
         hi = bf8(f.b[u][nt][0][0]);
@@ -271,7 +333,14 @@ __device__ __forceinline__ void mma_frags(const Frags<RT, NT, KU, NP, W>& f, uin
         acc[rt][nt] = mfma16(a, hi, acc[rt][nt]);
         acc[rt][nt] = mfma16(a, lo, acc[rt][nt]);
       }
+      }
     }
+  if constexpr (is_f32<W>()) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[rt][nt] += grp[rt][nt];
+  }
   __builtin_amdgcn_wave_barrier();
 }
 
@@ -309,12 +378,13 @@ struct TokSrc {
   uint32_t part;
   int tn;
 };
+template <class W>
 __device__ __forceinline__ TokSrc token_source(bool pre, const float* x, const uint4* xs, int C, int T, int ntt) {
   if (pre) {
     const uint32_t plane = 16u * (uint32_t)((C + 3) / 4) * (uint32_t)ntt * (uint32_t)kWave;
-    return TokSrc{make_buf(xs, 2 * plane), plane, ntt};
+    return TokSrc{make_buf(xs, is_f32<W>() ? plane : 2 * plane), plane, ntt};
   }
-  return TokSrc{make_buf(x, 32u * (uint32_t)T * (uint32_t)C), 0u, T};
+  return TokSrc{make_buf(x, tok_bytes<W>() * (uint32_t)T * (uint32_t)C), 0u, T};
 }
 
 // ------------------------------------------------------------------ token pre-split
@@ -324,13 +394,19 @@ __device__ __forceinline__ TokSrc token_source(bool pre, const float* x, const u
 // every value again.  This kernel writes the split once, in fragment order: entry
 // ((ks ntt + nt) 64 + lane) of the hi plane holds the bf16 hi parts of tokens
 // 16 nt + (lane & 15), elements 32 ks + 8 (lane >> 4) .. + 7, the lo plane (nks ntt 64
-// entries later) their lo parts; zero past the batch and past d.
+// entries later) their lo parts; zero past the batch and past d.  F32 (fp32 weights): one plane
+// of the fp32 values, elements 16 ks + 4 (lane >> 4) .. + 3.
+template <bool F32>
 __global__ __launch_bounds__(kBlock) void k_split_tokens(const float* __restrict__ x, int C, int T, int nks, int ntt,
                                                          uint4* __restrict__ xs) {
   const int n = nks * ntt * kWave, i = blockIdx.x * kBlock + threadIdx.x;
   if (i >= n) return;
   const int lane = i % kWave, fr = i / kWave, nt = fr % ntt, ks = fr / ntt;
   const int tok = 16 * nt + (lane & 15), c = 4 * ks + (lane >> 4);
+  if constexpr (F32) {
+    xs[i] = tok < T && c < C ? reinterpret_cast<const uint4*>(x)[(size_t)tok * C + c] : make_uint4(0u, 0u, 0u, 0u);
+    return;
+  }
   float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (tok < T && c < C) {
     const float4* p = reinterpret_cast<const float4*>(x + 8 * ((size_t)tok * C + c));
@@ -371,10 +447,10 @@ __global__ __launch_bounds__(kZWaves * kWave) void k_lopa_z_mfma(const float* __
   int roff[S::NI];
   stage_rows<1, KU, W>(roff, C, [&](int br) { return tile * 16 + br < r ? tile * 16 + br : -1; });
   const Buf ab = make_buf(A, 16u * (uint32_t)r * (uint32_t)(C / S::R8));
-  TokSrc tok = token_source(PRE, x, xs, C, T, ntt);
+  TokSrc tok = token_source<W>(PRE, x, xs, C, T, ntt);
   if constexpr (PRE) {  // the group's first token tile at entry 0 of each k step's row of tiles
     const uint32_t skip = 16u * (uint32_t)(tg * NT * kWave);
-    tok.b = make_buf(xs + (size_t)tg * NT * kWave, 2 * tok.part - skip);
+    tok.b = make_buf(xs + (size_t)tg * NT * kWave, (is_f32<W>() ? 1 : 2) * tok.part - skip);
   }
   f32x4_t acc[1][NT];
 #pragma unroll
@@ -403,17 +479,33 @@ __global__ __launch_bounds__(kZWaves * kWave) void k_lopa_z_mfma(const float* __
   }
 }
 
+// One wave's 16 entries: lane m + 16 g holds nz[i] of entry 4 g + i for the tokens m, 16 + m, ...;
+// bit 4 g + i of *out is set if any lane of the group holds true.
+__device__ __forceinline__ void put_alive(uint16_t* out, const bool (&nz)[4]) {
+  uint32_t mask = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint64_t b = __ballot(nz[i]);
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      if ((b >> (16 * g)) & 0xffffull) mask |= 1u << (4 * g + i);
+  }
+  if (lane_id() == 0) *out = (uint16_t)mask;
+}
+
 // ------------------------------------------------------------------ gate + union + W_up
 // Segments of at most 64 neurons, each workgroup taking every gridDim.x-th one.  Wave w
 // multiplies the segment's four row tiles over k part w; the parts are added in LDS,
 // wave w owning tile w.  A neuron joins the union if any token activates it (h > t;
 // NaN compares false); one ballot orders the union ascending.  The W_up dots of the
-// union rows use the same split, and zval = act * v goes to the fragment buffer of the
-// down kernel: per fragment group (segment, entries 32 gi .. 32 gi + 31) and token tile
-// a plane of 64 hi entries, then one of 64 lo entries; entry m + 16 g holds, for token
-// 16 nt + m, the bf16 parts of entries 4g .. 4g + 3 then 16 + 4g .. 16 + 4g + 3 of the
-// group.  A used group is written whole (zero past the union), an unused one is never
-// read.
+// union rows use the same split, and zval = act * v goes to the buffer of the down kernel by
+// quads of entries: quad 16 seg + k (entries 4 k .. 4 k + 3 of segment seg), token tile nt and
+// token 16 nt + m at uint4 ((16 seg + k) ntt + nt) 16 + m, the four values as bf16 hi parts then
+// lo parts (fp32 weights: as fp32).  A used quad is written whole (zero past the union), an
+// unused one is never read.
+// fp32 weights also leave alive[4 seg + k], bit j: entry 16 k + j of the segment has a value other
+// than 0 for some token.  The down kernel does not read the W_down rows of the other entries
+// (every entry counts as alive in a dense call), as the vector-ALU batch kernels do not.
 // LOPA: the gate rows are B [d_ff][r] against z = zp[0] + zp[1]; otherwise W_gate x.
 // KU / KUU: k steps per load group of the gate rows / the W_up rows.
 // FORM (a FormKind): the paper's full form (`form`): the activation value, SiLU on the
@@ -427,9 +519,10 @@ __device__ __forceinline__ void gate_up_body(const float* __restrict__ x, const 
                                              uint4* __restrict__ zf, float* __restrict__ y,
                                              const uint4* __restrict__ xs, int ntt, Form form,
                                              const float* __restrict__ gx, const float* __restrict__ s_g,
-                                             const float* __restrict__ s_up, const float* __restrict__ s_down) {
+                                             const float* __restrict__ s_up, const float* __restrict__ s_down,
+                                             uint16_t* __restrict__ alive) {
   constexpr bool Q = is_quant<W>();
-  constexpr int R8 = W::EPC / 8;
+  constexpr int R8 = W::EPC / tile_elems<W>();
   constexpr bool FULL = FORM != kFormDefault, HAS_G = FORM == kFormLoPA;
   constexpr bool PRE = NT > 1;  // tokens pre-split by k_split_tokens
   // the W_up rows of a union of at most two row tiles go as two tiles with twice the k
@@ -447,7 +540,7 @@ __device__ __forceinline__ void gate_up_body(const float* __restrict__ x, const 
   const int lane = lane_id(), wave = uniform(threadIdx.x / kWave);
   const int m = lane & 15, g = lane >> 4;
   clear_output(y, T * d, meta, nseg);
-  const TokSrc tok = token_source(PRE, x, xs, Cu, T, ntt);
+  const TokSrc tok = token_source<W>(PRE, x, xs, Cu, T, ntt);
   const Buf ub = make_buf(w_up, 16u * (uint32_t)d_ff * (uint32_t)(Cu / R8));
 
   // segments blockIdx.x, blockIdx.x + gridDim.x, ... (the host makes the counts equal)
@@ -469,7 +562,7 @@ __device__ __forceinline__ void gate_up_body(const float* __restrict__ x, const 
       kpart(Cg, wave, kParts, &ks0, &ks1);
       const Buf gb = make_buf(gate_w, 16u * (uint32_t)d_ff * (uint32_t)(Cg / R8));
       if constexpr (LOPA) {
-        const uint32_t part = 32u * (uint32_t)tc * (uint32_t)Cg;
+        const uint32_t part = tok_bytes<W>() * (uint32_t)tc * (uint32_t)Cg;
         stream_rows<kTiles, NT, KU, 2, false, W>(gb, Cg, roff, s_stage[wave], make_buf(zp, 2 * part), part, T, ks0,
                                                  ks1, acc);
       } else {
@@ -593,8 +686,7 @@ __device__ __forceinline__ void gate_up_body(const float* __restrict__ x, const 
         for (int nt = 0; nt < NT; ++nt) s_red[wave][rt][nt][lane] = acc[rt][nt];
     __syncthreads();
 
-    // wave w: union entries 16 w .. 16 w + 15 = half (w & 1) of fragment group w >> 1
-    const int gi = wave >> 1, half = wave & 1;
+    // wave w: union entries 16 w .. 16 w + 15, lane m + 16 g the quad of entries 16 w + 4 g ..
     // quantized: the W_up scale of each entry's row, and its W_down scale folded into zval
     float sue[4] = {1.f, 1.f, 1.f, 1.f}, sde[4] = {1.f, 1.f, 1.f, 1.f};
     if constexpr (Q) {
@@ -607,7 +699,8 @@ __device__ __forceinline__ void gate_up_body(const float* __restrict__ x, const 
         sde[i] = __builtin_bit_cast(float, ldb32(dbs, off));
       }
     }
-    if (32 * gi < cnt) {
+    bool nz[4] = {DENSE, DENSE, DENSE, DENSE};  // fp32 weights: the lane's entries, for its tokens
+    if (16 * wave + 4 * g < cnt) {
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
         const int tok = 16 * nt + m;
@@ -617,24 +710,26 @@ __device__ __forceinline__ void gate_up_body(const float* __restrict__ x, const 
               s_red[3][wave][nt][lane];
         if (tok < T) {
           uint32_t hw[2] = {0u, 0u}, lw[2] = {0u, 0u};
+          f32x4_t zv;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int e = 16 * wave + 4 * g + i;
             const float vu = Q ? v[i] * sue[i] : v[i];
             float zz = e < cnt ? s_act[s_list[e]][tok] * (FULL ? up_value(form.silu_up, vu) : vu) : 0.f;
             if constexpr (Q) zz *= sde[i];
+            zv[i] = zz;
+            nz[i] |= zz != 0.f;
             const __bf16 hb = (__bf16)zz;
             const __bf16 lb = (__bf16)(zz - (float)hb);
             hw[i >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, hb) << (16 * (i & 1));
             lw[i >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, lb) << (16 * (i & 1));
           }
-          // hi plane entry of lane m + 16 g, then the lo plane 64 entries on
-          uint4* frag = zf + ((((size_t)seg * 2 + gi) * ntt + nt) * 2) * kWave + m + 16 * g;
-          reinterpret_cast<uint2*>(frag)[half] = make_uint2(hw[0], hw[1]);
-          reinterpret_cast<uint2*>(frag + kWave)[half] = make_uint2(lw[0], lw[1]);
+          zf[(((size_t)seg * kSegQuads + 4 * wave + g) * ntt + nt) * 16 + m] =
+              is_f32<W>() ? __builtin_bit_cast(uint4, zv) : make_uint4(hw[0], hw[1], lw[0], lw[1]);
         }
       }
     }
+    if constexpr (is_f32<W>()) put_alive(alive + 4 * seg + wave, nz);
   }
 }
 
@@ -644,17 +739,17 @@ __device__ __forceinline__ void gate_up_body(const float* __restrict__ x, const 
       int32_t *__restrict__ meta, int32_t *__restrict__ seg_count, int32_t *__restrict__ seg_idx,                  \
       float *__restrict__ seg_act, uint4 *__restrict__ zf, float *__restrict__ y, const uint4 *__restrict__ xs,  \
       int ntt, Form form, const float *__restrict__ gx, const float *__restrict__ s_g,                            \
-      const float *__restrict__ s_up, const float *__restrict__ s_down
+      const float *__restrict__ s_up, const float *__restrict__ s_down, uint16_t *__restrict__ alive
 #define FFN_GATE_UP_ARGS                                                                                            \
   x, zp, gate_w, Cg, w_up, Cu, T, d, d_ff, nseg, t, slots, tc, meta, seg_count, seg_idx, seg_act, zf, y, xs, ntt, form, \
-      gx, s_g, s_up, s_down
+      gx, s_g, s_up, s_down, alive
 
 // One workgroup per CU: four k steps a group for one token tile (two for LoPA's short
 // gate rows and for wider token tiles; one for LoPA's gate rows with four token tiles,
 // whose fragments carry both partial copies of z).
 template <class W, bool LOPA, bool DENSE, int NT, int FORM>
 __global__ __launch_bounds__(kBlock) void k_gate_up_mfma(FFN_GATE_UP_PARAMS) {
-  constexpr int KU = NT == 1 ? (LOPA ? 2 : 4) : (LOPA && NT == 4 ? 1 : 2);
+  constexpr int KU = NT == 1 ? (LOPA && !is_f32<W>() ? 2 : 4) : (LOPA && NT == 4 && !is_f32<W>() ? 1 : 2);
   gate_up_body<W, LOPA, DENSE, NT, KU, NT == 1 ? 4 : 2, FORM>(FFN_GATE_UP_ARGS);
 }
 
@@ -667,7 +762,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
   gate_up_body<W, LOPA, DENSE, 1, 2, 2, FORM>(FFN_GATE_UP_ARGS);
 }
 // ------------------------------------------------------------------ batches of 2 .. 4 tokens
-// For at most four tokens the gate and the W_up dots run on v_mfma_f32_4x4x4_16b_bf16:
+// For at most four tokens the gate and the W_up dots run on v_mfma_f32_4x4x4_16b_bf16 (fp32 rows:
+// v_mfma_f32_4x4x1_16b_f32, four a chunk; d 3840, d_ff 14231, LoPA r = 480, 2 / 4 tokens 31.7 /
+// 33.3 us on the 16x16x4 kernel -> 21.5 / 27.2 us):
 // sixteen independent 4x4x4 products an instruction, in which lane 4b + i holds 4
 // consecutive k of row i of block b (A operand), lane 4b + j those of token j (B operand),
 // and element i of lane 4b + j receives D[b][i][j].  One load instruction of a quad (four
@@ -703,8 +800,17 @@ __device__ __forceinline__ f32x4_t mfma4(short4_t a, short4_t b, f32x4_t c) {
 // fragment at t: t[f kWave], f < FW / 2 the hi parts, then as many lo parts.  Four accumulators take the
 // hi and lo products of the two k halves of each group, so that no product waits on the
 // one before it.
+// fp32 rows: component c of the chunk in accumulator c (products of one k: 4x4x1).
 template <class W>
 __device__ __forceinline__ void q4_mma(const uint4& v, const uint4* __restrict__ t, f32x4_t (&acc)[4]) {
+  if constexpr (is_f32<W>()) {
+    const uint4 b = t[0];
+    acc[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(comp<0>(v), comp<0>(b), acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(comp<1>(v), comp<1>(b), acc[1], 0, 0, 0);
+    acc[2] = __builtin_amdgcn_mfma_f32_4x4x1f32(comp<2>(v), comp<2>(b), acc[2], 0, 0, 0);
+    acc[3] = __builtin_amdgcn_mfma_f32_4x4x1f32(comp<3>(v), comp<3>(b), acc[3], 0, 0, 0);
+    return;
+  } else {
   constexpr int G8 = W::EPC / 8, FW = W::EPC / 4;
   auto one = [&](const uint4& w, const uint4& th, const uint4& tl) {
     acc[0] = mfma4(half4(w, 0), half4(th, 0), acc[0]);
@@ -717,6 +823,7 @@ __device__ __forceinline__ void q4_mma(const uint4& v, const uint4* __restrict__
   if constexpr (G8 > 2) {
     one(bf16_chunk<W, 2>(v), t[2 * kWave], t[(FW / 2 + 2) * kWave]);
     one(bf16_chunk<W, 3>(v), t[3 * kWave], t[(FW / 2 + 3) * kWave]);
+  }
   }
 }
 
@@ -794,10 +901,12 @@ __device__ __forceinline__ void q4_load_tokens(const float* __restrict__ src, in
     const int unit = threadIdx.x + u * kQ4Threads, j = unit % 4, k = 8 * (unit / 4);
     const bool ok = unit < nu && j < T && k < K;
     const uint32_t off = ok ? 4u * ((uint32_t)j * (uint32_t)stride + (uint32_t)k) : kOOB;
-    float4 a = __builtin_bit_cast(float4, ldb(sb, off)), c = __builtin_bit_cast(float4, ldb(sb, off + 16));
+    const bool ok2 = ok && (W::EPC > 4 || k + 4 < K);  // fp32 rows may end in half a unit
+    const uint32_t off2 = ok2 ? off + 16 : kOOB;
+    float4 a = __builtin_bit_cast(float4, ldb(sb, off)), c = __builtin_bit_cast(float4, ldb(sb, off2));
     if (copies == 2) {
       const float4 a2 = __builtin_bit_cast(float4, ldb(sb, ok ? off + 4u * part : kOOB));
-      const float4 c2 = __builtin_bit_cast(float4, ldb(sb, ok ? off + 4u * part + 16 : kOOB));
+      const float4 c2 = __builtin_bit_cast(float4, ldb(sb, ok2 ? off2 + 4u * part : kOOB));
       a = make_float4(a.x + a2.x, a.y + a2.y, a.z + a2.z, a.w + a2.w);
       c = make_float4(c.x + c2.x, c.y + c2.y, c.z + c2.z, c.w + c2.w);
     }
@@ -812,7 +921,11 @@ __device__ __forceinline__ void q4_store_tokens(const float4 (&v)[UMAX][2], int 
 #pragma unroll
   for (int u = 0; u < UMAX; ++u) {
     const int unit = threadIdx.x + u * kQ4Threads, j = unit % 4, k = 8 * (unit / 4);
-    if (unit < nu) {
+    if (is_f32<W>() && unit < nu) {  // two chunks of 4
+      uint4* p = tok + (size_t)(k / (16 * EPC)) * kWave + 4 * ((k / EPC) % 16) + j;
+      p[0] = __builtin_bit_cast(uint4, v[u][0]);
+      p[4] = __builtin_bit_cast(uint4, v[u][1]);
+    } else if (unit < nu) {
       const float f[8] = {v[u][0].x, v[u][0].y, v[u][0].z, v[u][0].w, v[u][1].x, v[u][1].y, v[u][1].z, v[u][1].w};
       bf16x8_t hi, lo;
       split8(f, hi, lo);
@@ -844,7 +957,8 @@ __global__ __launch_bounds__(kQ4Threads) void k_gate_up_q4(FFN_GATE_UP_PARAMS) {
   const int lane = lane_id(), wave = uniform(threadIdx.x / kWave);
   for (int j = blockIdx.x * kQ4Threads + threadIdx.x; j < T * d; j += gridDim.x * kQ4Threads) y[j] = 0.f;
   if (blockIdx.x == 0 && threadIdx.x == 0) meta[0] = nseg;
-  const int Cu_ = Cu / (EPC / 8), Cg_ = Cg / (EPC / 8);
+  constexpr int TE = tile_elems<W>();
+  const int Cu_ = Cu / (EPC / TE), Cg_ = Cg / (EPC / TE);
   const int nsu = (Cu_ + 15) / 16, Kpx = nsu * STEP, nsg = (Cg_ + 15) / 16, Kpz = LOPA ? nsg * STEP : 0;
   uint4* const tok_g = s_tok + (LOPA ? Kpx : 0);
   const Buf gb = make_buf(gate_w, 16u * (uint32_t)d_ff * (uint32_t)Cg_);
@@ -880,7 +994,7 @@ __global__ __launch_bounds__(kQ4Threads) void k_gate_up_q4(FFN_GATE_UP_PARAMS) {
         float4 vx[UX][2];
         q4_load_tokens<W, UX>(x, T, d, Kpx, d, vx);
         float4 vz[UZ][2];
-        if constexpr (LOPA) q4_load_tokens<W, UZ>(zp, T, Cg * 8, Kpz, Cg * 8, vz, 2, (uint32_t)tc * (uint32_t)Cg * 8u);
+        if constexpr (LOPA) q4_load_tokens<W, UZ>(zp, T, Cg * TE, Kpz, Cg * TE, vz, 2, (uint32_t)(tc * Cg * TE));
         q4_store_tokens<W, UX>(vx, Kpx, s_tok);
         if constexpr (LOPA) q4_store_tokens<W, UZ>(vz, Kpz, tok_g);
         __syncthreads();
@@ -948,10 +1062,8 @@ __global__ __launch_bounds__(kQ4Threads) void k_gate_up_q4(FFN_GATE_UP_PARAMS) {
     }
     __syncthreads();
 
-    // wave w: union entries 16 w .. 16 w + 15 = half (w & 1) of fragment group w >> 1;
-    // lane m + 16 g: token m, entries 16 w + 4 g + i
+    // wave w < 4: union entries 16 w .. 16 w + 15, lane m + 16 g: token m, quad 4 w + g
     const int m = lane & 15, g = lane >> 4;
-    const int gi = wave >> 1, half = wave & 1;
     float sue[4] = {1.f, 1.f, 1.f, 1.f}, sde[4] = {1.f, 1.f, 1.f, 1.f};
     if constexpr (Q) {
       const Buf ubs = make_buf(s_up, 4u * (uint32_t)d_ff), dbs = make_buf(s_down, 4u * (uint32_t)d_ff);
@@ -963,28 +1075,32 @@ __global__ __launch_bounds__(kQ4Threads) void k_gate_up_q4(FFN_GATE_UP_PARAMS) {
         sde[i] = __int_as_float(ldb32(dbs, off));
       }
     }
-    if (wave < 4 && 32 * gi < cnt && m < T) {
+    bool nz[4] = {DENSE, DENSE, DENSE, DENSE};
+    if (wave < 4 && 16 * wave + 4 * g < cnt && m < T) {
       const int qq = 4 * wave + g;  // the quad of entries 16 w + 4 g ..
       f32x4_t v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int w = 0; w < kQ4Waves; ++w) v += s_pu[w][qq][m];
       uint32_t hw[2] = {0u, 0u}, lw[2] = {0u, 0u};
+      f32x4_t zv;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int e = 16 * wave + 4 * g + i;
         const float vu = Q ? v[i] * sue[i] : v[i];
         float zz = e < cnt ? s_act[s_list[e]][m] * (FULL ? up_value(form.silu_up, vu) : vu) : 0.f;
         if constexpr (Q) zz *= sde[i];
+        zv[i] = zz;
+        nz[i] |= zz != 0.f;
         const __bf16 hb = (__bf16)zz;
         const __bf16 lb = (__bf16)(zz - (float)hb);
         hw[i >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, hb) << (16 * (i & 1));
         lw[i >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, lb) << (16 * (i & 1));
       }
-      // token tile 0: hi plane entry of lane m + 16 g, then the lo plane 64 entries on
-      uint4* frag = zf + (((size_t)seg * 2 + gi) * ntt * 2) * kWave + m + 16 * g;
-      reinterpret_cast<uint2*>(frag)[half] = make_uint2(hw[0], hw[1]);
-      reinterpret_cast<uint2*>(frag + kWave)[half] = make_uint2(lw[0], lw[1]);
+      zf[((size_t)seg * kSegQuads + qq) * ntt * 16 + m] =
+          is_f32<W>() ? __builtin_bit_cast(uint4, zv) : make_uint4(hw[0], hw[1], lw[0], lw[1]);
     }
+    if constexpr (is_f32<W>())
+      if (wave < 4) put_alive(alive + 4 * seg + wave, nz);
   }
 }
 
@@ -994,63 +1110,69 @@ __global__ __launch_bounds__(kQ4Threads) void k_gate_up_q4(FFN_GATE_UP_PARAMS) {
 // ------------------------------------------------------------------ down projection
 // Workgroup b: column group b % S, row chunk b / S (a balanced share of the segments).
 // A wave owns DT 32-column tiles (DT = 4 for one token tile, else 2); a column group
-// is CW of them, and wave w takes column slot w % CW and every (4 / CW)-th used
-// fragment group of the chunk (32 union entries of one segment).  A group's 32 W_down
-// rows are read (64 / 4 DT) rows x 64 DT bytes per instruction, streamed past the
-// caches, and written to a wave-private LDS tile; transposing LDS reads
+// is CW of them, and wave w takes column slot w % CW and every (4 / CW)-th group of the
+// chunk.  The chunk's union entries are packed into groups of 32: each segment's list is
+// padded to whole quads of entries and the quads of all segments follow one another, eight a
+// group.  (A group had been 32 entries of one segment, where at two to four tokens and 90% a
+// segment's 11 - 20 entries left most of it empty: fp32 rows, d 3840, d_ff 14231, 2 / 4 tokens
+// 22.6 / 24.5 -> 15.2 / 20.5 us; bf16 rows, 4 tokens 15.3 -> 14.5 us, 64 tokens 0.7 us less.)
+// A group's 32 W_down rows are read (64 / 4 DT) rows x 64 DT bytes per instruction, streamed
+// past the caches, and written to a wave-private LDS tile; transposing LDS reads
 // (ds_read_b64_tr_b16) then hand every lane the 8 entries of one column that the
-// matrix-core B operand takes.  The chunk's slot indices and a table of its groups are
-// staged in LDS once; the loop reads a group's table entry two groups ahead and its slot
-// indices one group ahead, so the weight loads of the next group issue without waiting
-// on LDS.  The waves' sums meet in LDS, then go to y with one fp32 atomic per token and
-// column (y was cleared by the gate kernel).
-constexpr int kDnSlots = 4096;  // most slot indices of one row chunk
+// matrix-core B operand takes (fp32 weights: see dn_mma).  The packed rows and their zval
+// quads are listed in LDS once; the loop reads a group's entries one group ahead, so the
+// weight loads of the next group issue without waiting on LDS.  The waves' sums meet in LDS,
+// then go to y with one fp32 atomic per token and column (y was cleared by the gate kernel).
+constexpr int kDnSlots = 4096;  // most rows of one row chunk
+// LDS entries of the packed list: the rows, up to three pad entries a segment (at most kBlock
+// segments), and empty entries for the groups past the last one that the loop looks at
+constexpr int kDnPad = 4 * kParts;
+constexpr int kDnList = kDnSlots + 3 * kBlock + 32 * (kDnPad + 1);
 
 template <int NT, class W = WBf16>
 struct DnCfg {
-  static constexpr int DT = NT == 1 ? 4 : 2;  // 32-column tiles per wave
+  static constexpr bool F32 = is_f32<W>();
+  static constexpr int DT = NT == 1 && !F32 ? 4 : 2;  // 32-column tiles per wave
   static constexpr int CW = NT == 4 ? 1 : 2;  // column slots per workgroup
   static constexpr int WCOLS = 32 * DT * CW;  // columns per workgroup
-  static constexpr int R8 = W::EPC / 8;       // tile chunks (8 bf16) per loaded chunk
-  static constexpr int LPR = 4 * DT / R8;     // lanes per row of a load instruction
+  static constexpr int R8 = W::EPC / tile_elems<W>();  // tile chunks per loaded chunk
+  static constexpr int LPR = 32 * DT / W::EPC;  // lanes per row of a load instruction
   static constexpr int RPI = kWave / LPR;     // rows per load instruction
   static constexpr int NI = 32 / RPI;         // load instructions per group
   // chunks per LDS row: two pad chunks put the 8 rows that a half-wave's transposing
   // reads touch on distinct banks
-  static constexpr int PITCH = 4 * DT + 2;
+  static constexpr int PITCH = F32 ? 0 : 4 * DT + 2;
+  // the entry of a group that lane `lane` loads with instruction i
+  static __device__ __forceinline__ int entry(int i, int lane) {
+    return F32 ? 16 * (i >> 2) + 4 * (lane >> 4) + (i & 3) : RPI * i + lane / LPR;
+  }
 };
 
 template <int NT, class W = WBf16>
 struct DnFrags {
   uint4 t[DnCfg<NT, W>::NI];  // W_down chunks as loaded: entry RPI i + lane / LPR, chunk lane % LPR
-  uint4 zh[NT], zl[NT];       // zval fragments (hi, lo) of the token tiles
+  u32x4_t z[NT][2];           // zval quads of the token tiles
 };
-
-// A group's table entry: x = first slot (relative to the chunk's first row) | entries
-// << 16, y = the group's index in the zval fragment buffer.  The kDnPad table entries
-// past the last group are empty, so every load of such a group reads nothing.
-constexpr int kDnPad = 4 * kParts;
 
 template <int NT, class W = WBf16>
 struct DnRows {
   int row[DnCfg<NT, W>::NI];  // neuron of the entry this lane loads, -1 for none
-  int2 info;
+  int zq[2];                  // zval quads of the lane group: entries 4 g .. and 16 + 4 g .., -1 for none
 };
 
 // C: loaded chunks per row, ch: this lane's chunk
 template <int NT, class W>
-__device__ __forceinline__ DnRows<NT, W> dn_rows(int2 info, const int* s_idx, int C, int ch) {
+__device__ __forceinline__ DnRows<NT, W> dn_rows(int group, const int* s_row, const int* s_zq, int C, int ch) {
   using K = DnCfg<NT, W>;
-  const int lane = lane_id(), base = info.x & 0xFFFF, cnt = info.x >> 16;
+  const int lane = lane_id();
   DnRows<NT, W> a;
-  a.info = info;
 #pragma unroll
   for (int i = 0; i < K::NI; ++i) {
-    const int e = K::RPI * i + lane / K::LPR;
-    const bool ok = e < cnt && ch < C;
-    const int v = s_idx[ok ? base + e : 0];
-    a.row[i] = ok ? v : -1;
+    const int v = s_row[32 * group + K::entry(i, lane)];
+    a.row[i] = ch < C ? v : -1;
   }
+  a.zq[0] = s_zq[8 * group + (lane >> 4)];
+  a.zq[1] = s_zq[8 * group + 4 + (lane >> 4)];
   return a;
 }
 
@@ -1061,15 +1183,14 @@ __device__ __forceinline__ void dn_issue(DnFrags<NT, W>& f, const DnRows<NT, W>&
   const int lane = lane_id(), m = lane & 15;
 #pragma unroll
   for (int i = 0; i < K::NI; ++i) f.t[i] = ldb_nt(db, a.row[i] >= 0 ? 16u * (uint32_t)(a.row[i] * C + ch) : kOOB);
-  const bool has = a.info.x >> 16 > 0;
-  const uint32_t zg = (uint32_t)a.info.y * (uint32_t)ntt;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int tok = 16 * nt + m;
-    const uint32_t off = (has && tok < T) ? 16u * (((zg + nt) * 2) * kWave + lane) : kOOB;
-    f.zh[nt] = ldb(zb, off);
-    f.zl[nt] = ldb(zb, off + 16 * kWave);
-  }
+  for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      f.z[nt][h] = __builtin_bit_cast(
+          u32x4_t, ldb(zb, a.zq[h] >= 0 && 16 * nt + m < T
+                               ? 256u * ((uint32_t)a.zq[h] * (uint32_t)ntt + (uint32_t)nt) + 16u * (uint32_t)m
+                               : kOOB));
 }
 
 __device__ __forceinline__ uint2 lds_read_tr16(const char* p) {
@@ -1077,17 +1198,57 @@ __device__ __forceinline__ uint2 lds_read_tr16(const char* p) {
   return __builtin_bit_cast(uint2, v);
 }
 
+template <int I>
+struct Int {
+  static constexpr int value = I;
+};
+
 // tile: this wave's LDS tile (32 PITCH uint4).  Within each 16-lane group q of the
 // transposing read, lane 4a + b addresses 8 bytes (4 columns) of one tile row and lane
 // 4b + c receives element c of the chunks of lanes b, 4 + b, 8 + b, 12 + b.  With lane
 // 4a + b pointing at entry 4q + a (then 16 + 4q + a), columns 4b .. 4b + 3 of a 16-column
 // block, lane n of the group ends with entries 4q .. 4q + 3 (then 16 + 4q ..) of column
-// n: the B operand in the entry order of the zval fragments.
+// n: the B operand in the entry order of the zval quads (see DnRows).
 template <int NT, class W>
 __device__ __forceinline__ void dn_mma(const DnFrags<NT, W>& f, uint4* tile,
                                        f32x4_t (&acc)[DnCfg<NT, W>::DT][2][NT]) {
   using K = DnCfg<NT, W>;
+  if constexpr (K::F32) {
+    // A lane's 16 bytes of entry e are columns 4 n .. 4 n + 3 (n = lane & 15): component c of
+    // load i is the B operand of the product over the entries of load i for the columns 4 n + c,
+    // so the rows need no reshaping.  Sums of component c go to acc[c / 2][c % 2], the group's
+    // own first (see is_f32).
+    f32x4_t grp[4][NT];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) grp[c][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    auto load = [&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const float z = __uint_as_float(f.z[nt][i >> 2][i & 3]);
+        grp[0][nt] = mfma16f(z, comp<0>(f.t[i]), grp[0][nt]);
+        grp[1][nt] = mfma16f(z, comp<1>(f.t[i]), grp[1][nt]);
+        grp[2][nt] = mfma16f(z, comp<2>(f.t[i]), grp[2][nt]);
+        grp[3][nt] = mfma16f(z, comp<3>(f.t[i]), grp[3][nt]);
+      }
+    };
+    load(Int<0>{}), load(Int<1>{}), load(Int<2>{}), load(Int<3>{});
+    load(Int<4>{}), load(Int<5>{}), load(Int<6>{}), load(Int<7>{});
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[c / 2][c % 2][nt] += grp[c][nt];
+    return;
+  } else {
   constexpr int ROWB = 16 * K::PITCH;  // bytes per tile row
+  bf16x8_t zh[NT], zl[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    zh[nt] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(f.z[nt][0], f.z[nt][1], 0, 1, 4, 5));
+    zl[nt] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(f.z[nt][0], f.z[nt][1], 2, 3, 6, 7));
+  }
   const int lane = lane_id();
 #pragma unroll
   for (int i = 0; i < K::NI; ++i)  // quantized rows: the codes as bf16, R8 tile chunks a loaded chunk
@@ -1103,11 +1264,12 @@ __device__ __forceinline__ void dn_mma(const DnFrags<NT, W>& f, uint4* tile,
       const bf16x8_t b = bf8(make_uint4(lo.x, lo.y, hi.x, hi.y));
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
-        acc[ct][h][nt] = mfma16(bf8(f.zh[nt]), b, acc[ct][h][nt]);
-        acc[ct][h][nt] = mfma16(bf8(f.zl[nt]), b, acc[ct][h][nt]);
+        acc[ct][h][nt] = mfma16(zh[nt], b, acc[ct][h][nt]);
+        acc[ct][h][nt] = mfma16(zl[nt], b, acc[ct][h][nt]);
       }
     }
   __builtin_amdgcn_wave_barrier();
+  }
 }
 
 // C: loaded chunks per row of w_down_t (d / W::EPC); the W_down row scales of quantized
@@ -1117,22 +1279,24 @@ __global__ __launch_bounds__(kBlock) void k_down_mfma(const int32_t* __restrict_
                                                       const int32_t* __restrict__ seg_idx,
                                                       const uint4* __restrict__ zf, int nseg, int d_ff, int R, int tc,
                                                       const uint4* __restrict__ w_down_t, int C, int d, int T,
-                                                      float* __restrict__ y) {
+                                                      float* __restrict__ y, const uint2* __restrict__ alive) {
   using K = DnCfg<NT, W>;
   constexpr int CW = K::CW, GS = kParts / CW, WCOLS = K::WCOLS;
   const Buf db = make_buf(w_down_t, 16u * (uint32_t)d_ff * (uint32_t)C);
   const int ntt = (tc + 15) / 16;
   const Buf zb = make_buf(zf, 4096u * (uint32_t)nseg * (uint32_t)ntt);
-  // LDS: the waves' tiles and the chunk's slot indices during the loop; afterwards the
+  // LDS: the waves' tiles and the chunk's packed list during the loop; afterwards the
   // same space holds every wave's sums, [wave][ct][h][nt][lane] as f32x4
-  constexpr int STAGE_U4 = kParts * 32 * K::PITCH, IDX_U4 = kDnSlots / 4;
+  constexpr int STAGE_U4 = kParts * 32 * K::PITCH, IDX_U4 = (kDnList + kDnList / 4 + 3) / 4;
   constexpr int PART_U4 = kParts * K::DT * 2 * NT * kWave;
   constexpr int BIG_U4 = STAGE_U4 + IDX_U4 > PART_U4 ? STAGE_U4 + IDX_U4 : PART_U4;
   __shared__ uint4 s_big[BIG_U4];
-  __shared__ int s_wgrp[kBlock / kWave];
-  __shared__ int2 s_ginfo[2 * kBlock + kDnPad];
+  __shared__ int s_wquads[kBlock / kWave];
+  __shared__ int s_cnt[kBlock], s_quad[kBlock];  // per segment of the chunk: entries, first quad
+  __shared__ uint2 s_alive[K::F32 ? kBlock : 1];  // fp32 weights: a bit an entry whose row is read
   uint4* const s_stage = s_big;
-  int* const s_idx = reinterpret_cast<int*>(s_big + STAGE_U4);
+  int* const s_row = reinterpret_cast<int*>(s_big + STAGE_U4);
+  int* const s_zq = s_row + kDnList;
   f32x4_t* const s_part = reinterpret_cast<f32x4_t*>(s_big);
 
   const int S = (d + WCOLS - 1) / WCOLS;
@@ -1145,45 +1309,62 @@ __global__ __launch_bounds__(kBlock) void k_down_mfma(const int32_t* __restrict_
   const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid / kWave);
   const int slot_w = wave % CW, phase = wave / CW;
 
-  // segment tid of the chunk has (c > 0) + (c > 32) fragment groups; their places in
-  // the group table come from two ballots and the per-wave totals
-  const int c = tid < nsc ? seg_count[seg_lo + tid] : 0;
-  const int srow = tid < nsc ? segs.start(seg_lo + tid) - row_lo : 0;
-  {
-    // eight loads in flight per thread before their LDS stores
-    const Buf ib = make_buf(seg_idx + row_lo, 4u * (uint32_t)nslot);
-    for (int o0 = 0; o0 < nslot; o0 += 8 * kBlock) {
-      int v[8];
+  // The packed list: wave w takes the chunk's segments w, w + 4, ..., a lane an entry (segments
+  // have at most 64 rows), SU of them in flight.  The first ones are requested ahead of the
+  // counts' scan.
+  constexpr int SU = 8;
+  const Buf ib = make_buf(seg_idx + row_lo, 4u * (uint32_t)nslot);
+  auto fetch = [&](int (&v)[SU], int s0) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int o = o0 + u * kBlock + tid;
-        v[u] = ldb32(ib, o < nslot ? 4u * (uint32_t)o : kOOB);
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int o = o0 + u * kBlock + tid;
-        if (o < nslot) s_idx[o] = v[u];
-      }
+    for (int u = 0; u < SU; ++u) {
+      const int sg = s0 + u * kParts, sl = sg < nsc ? sg : 0;
+      const int at = segs.start(seg_lo + sl) - row_lo + lane;
+      v[u] = ldb32(ib, sg < nsc && at < nslot ? 4u * (uint32_t)at : kOOB);
     }
-  }
-  const uint64_t has1 = __ballot(c > 0), has2 = __ballot(c > 32);
-  if (lane == 0) s_wgrp[wave] = __popcll(has1) + __popcll(has2);
+  };
+  int v0[SU];
+  const int c = tid < nsc ? seg_count[seg_lo + tid] : 0;
+  uint2 live = make_uint2(0u, 0u);
+  if constexpr (K::F32)
+    if (tid < nsc) live = alive[seg_lo + tid];
+  fetch(v0, wave);
+  const int quads = wave_inclusive_scan((c + 3) >> 2);
+  if (lane == kWave - 1) s_wquads[wave] = quads;
   __syncthreads();
-  int gbase = 0, ngrp = 0;
+  int qbase = 0, nquad = 0;
 #pragma unroll
   for (int w = 0; w < kBlock / kWave; ++w) {
-    const int v = s_wgrp[w];
-    gbase += w < wave ? v : 0;
-    ngrp += v;
+    const int v = s_wquads[w];
+    qbase += w < wave ? v : 0;
+    nquad += v;
   }
-  ngrp = uniform(ngrp);
-  if (tid < nsc) {
-    const int b = gbase + rank_in_mask(has1) + rank_in_mask(has2);
-    const int zg = 2 * (seg_lo + tid);
-    if (c > 0) s_ginfo[b] = make_int2(srow | (min(c, 32) << 16), zg);
-    if (c > 32) s_ginfo[b + 1] = make_int2((srow + 32) | ((c - 32) << 16), zg + 1);
+  nquad = uniform(nquad);
+  const int ngrp = (nquad + 7) / 8;
+  s_cnt[tid] = c;
+  if constexpr (K::F32) s_alive[tid] = live;
+  s_quad[tid] = qbase + quads - ((c + 3) >> 2);
+  for (int o = 4 * nquad + tid; o < 32 * (ngrp + kDnPad); o += kBlock) {
+    s_row[o] = -1;
+    if ((o & 3) == 0) s_zq[o >> 2] = -1;
   }
-  if (tid < kDnPad) s_ginfo[ngrp + tid] = make_int2(0, 0);
+  __syncthreads();
+  for (int s0 = wave;; s0 += kParts * SU) {
+#pragma unroll
+    for (int u = 0; u < SU; ++u) {
+      const int sg = s0 + u * kParts;
+      if (sg < nsc) {
+        const int n = s_cnt[sg], o = 4 * s_quad[sg] + lane;
+        if (lane < ((n + 3) & ~3)) {
+          bool read = lane < n;
+          if constexpr (K::F32) read = read && (((lane < 32 ? s_alive[sg].x : s_alive[sg].y) >> (lane & 31)) & 1u);
+          s_row[o] = read ? v0[u] : -1;
+          if ((lane & 3) == 0) s_zq[o >> 2] = kSegQuads * (seg_lo + sg) + (lane >> 2);
+        }
+      }
+    }
+    if (s0 + kParts * SU >= nsc) break;
+    fetch(v0, s0 + kParts * SU);
+  }
   __syncthreads();
 
   f32x4_t acc[K::DT][2][NT];
@@ -1197,25 +1378,22 @@ __global__ __launch_bounds__(kBlock) void k_down_mfma(const int32_t* __restrict_
   // this lane's 16-byte chunk of the wave's columns
   const int ch = (cgrp * WCOLS + slot_w * 32 * K::DT) / W::EPC + lane % K::LPR;
   if (phase < ngrp) {
-    // two register sets alternate, one group each per half-iteration; the table entry of
-    // group j + 3 GS and the slot indices of group j + 2 GS are read while group j is
-    // multiplied.  A pair always multiplies both halves (a group past the last one loads
-    // nothing and adds zeros), so no load sits on a conditional path.
+    // two register sets alternate, one group each per half-iteration; the list entries of group
+    // j + 2 GS are read while group j is multiplied.  A pair always multiplies both halves (a
+    // group past the last one loads nothing and adds zeros), so no load sits on a conditional
+    // path.
     DnFrags<NT, W> f0, f1;
-    DnRows<NT, W> a = dn_rows<NT, W>(s_ginfo[phase], s_idx, C, ch);
+    DnRows<NT, W> a = dn_rows<NT, W>(phase, s_row, s_zq, C, ch);
     dn_issue(f0, a, db, zb, C, ch, T, ntt);
-    a = dn_rows<NT, W>(s_ginfo[phase + GS], s_idx, C, ch);
-    int2 info = s_ginfo[phase + 2 * GS];
+    a = dn_rows<NT, W>(phase + GS, s_row, s_zq, C, ch);
     for (int j = phase;; j += 2 * GS) {
       dn_issue(f1, a, db, zb, C, ch, T, ntt);
       issue_barrier();
-      a = dn_rows<NT, W>(info, s_idx, C, ch);
-      info = s_ginfo[j + 3 * GS];
+      a = dn_rows<NT, W>(j + 2 * GS, s_row, s_zq, C, ch);
       dn_mma(f0, s_stage + wave * 32 * K::PITCH, acc);
       dn_issue(f0, a, db, zb, C, ch, T, ntt);
       issue_barrier();
-      a = dn_rows<NT, W>(info, s_idx, C, ch);
-      info = s_ginfo[j + 4 * GS];
+      a = dn_rows<NT, W>(j + 3 * GS, s_row, s_zq, C, ch);
       dn_mma(f1, s_stage + wave * 32 * K::PITCH, acc);
       if (j + 2 * GS >= ngrp) break;
     }
@@ -1233,10 +1411,21 @@ __global__ __launch_bounds__(kBlock) void k_down_mfma(const int32_t* __restrict_
   __syncthreads();
   constexpr int NE = CW * K::DT * 2 * NT * kWave;
   for (int o = tid; o < NE; o += kBlock) {
-    const int l = o % kWave, r = o / kWave;  // r = ((slot DT + ct) 2 + h) NT + nt
-    const int nt = r % NT, h = (r / NT) % 2, ct = (r / (2 * NT)) % K::DT, slot = r / (2 * NT * K::DT);
+    int l = o % kWave, r = o / kWave;  // r = ((slot DT + ct) 2 + h) NT + nt
+    const int nt = r % NT;
+    int h = (r / NT) % 2, ct = (r / (2 * NT)) % K::DT;
+    const int slot = r / (2 * NT * K::DT);
+    int cc = 32 * ct + 16 * h + (l & 15);
+    if constexpr (K::F32) {
+      // 64 consecutive columns of four tokens: thread l takes column l of the slot, component
+      // l % 4 of lane l / 4, and 2 ct + h picks the token quad
+      const int q = 2 * ct + h;
+      cc = l;
+      ct = (l >> 1) & 1, h = l & 1;
+      l = (l >> 2) + 16 * q;
+    }
     const int tok0 = 16 * nt + 4 * (l >> 4);
-    const int col = cgrp * WCOLS + slot * 32 * K::DT + 32 * ct + 16 * h + (l & 15);
+    const int col = cgrp * WCOLS + slot * 32 * K::DT + cc;
     if (tok0 >= T || col >= d) continue;
     f32x4_t v = s_part[(((slot * K::DT + ct) * 2 + h) * NT + nt) * kWave + l];
 #pragma unroll
@@ -1248,18 +1437,23 @@ __global__ __launch_bounds__(kBlock) void k_down_mfma(const int32_t* __restrict_
 }
 
 // ------------------------------------------------------------------ host side
+// fp32 weights: the entries' alive bits, 8 bytes a segment, in the space of seg_zval, which this path
+// does not use otherwise (4 d_ff bytes a token, at least 256; segments are of 64 rows, or at most
+// 512 of them where d_ff > 8192)
+uint16_t* alive_masks(const Workspace& ws) { return reinterpret_cast<uint16_t*>(ws.seg_zval); }
 int token_tiles(const Workspace& ws) { return (ws.tc + 15) / 16; }
 
+template <bool F32>
 hipError_t split_tokens(const Shape& sh, const float* x, const Workspace& ws, hipStream_t s) {
-  const int C = sh.d / 8, nks = (C + 3) / 4, ntt = token_tiles(ws);
+  const int C = sh.d / (F32 ? 4 : 8), nks = (C + 3) / 4, ntt = token_tiles(ws);
   const int n = nks * ntt * kWave;
-  k_split_tokens<<<(n + kBlock - 1) / kBlock, kBlock, 0, s>>>(x, C, sh.T, nks, ntt, ws.xs);
+  k_split_tokens<F32><<<(n + kBlock - 1) / kBlock, kBlock, 0, s>>>(x, C, sh.T, nks, ntt, ws.xs);
   return hipGetLastError();
 }
 template <class W, int NT, bool PRE>
 hipError_t z_mfma(const Shape& sh, const Form& form, const float* x, const void* lopa_a, const Workspace& ws,
                   hipStream_t s) {
-  const int C = sh.d / 8, ngrp = PRE ? token_tiles(ws) / NT : 1, grid = ((sh.r + 15) / 16) * kZParts * ngrp;
+  const int C = sh.d / tile_elems<W>(), ngrp = PRE ? token_tiles(ws) / NT : 1, grid = ((sh.r + 15) / 16) * kZParts * ngrp;
   // with G, extra workgroups write G x for the gate kernel
   const GWork gw{form, x, ws.gx, sh.T, sh.d, sh.d_ff, grid};
   const int g = grid + (form.g_idx ? (g_items(sh.d_ff, sh.T) + kZWaves * kWave - 1) / (kZWaves * kWave) : 0);
@@ -1286,7 +1480,7 @@ bool q4_fits(const Shape& sh, bool lopa) {
 template <class W, bool LOPA, bool DENSE, int NT, int FORM>
 hipError_t gate_mfma(const Shape& sh, const Form& form, const float* x, const void* gate_w, const void* w_up, float t,
                      Workspace& ws, float* y, hipStream_t s) {
-  const int Cu = sh.d / 8, Cg = LOPA ? sh.r / 8 : Cu;
+  const int Cu = sh.d / tile_elems<W>(), Cg = LOPA ? sh.r / tile_elems<W>() : Cu;
   if constexpr (NT == 1)
     if (q4_fits<W>(sh, LOPA)) {
       ws.nseg = segments_for(sh.d_ff, kSegGrid);
@@ -1295,7 +1489,7 @@ hipError_t gate_mfma(const Shape& sh, const Form& form, const float* x, const vo
                                 (const float*)ws.z, static_cast<const uint4*>(gate_w), Cg,
                                 static_cast<const uint4*>(w_up), Cu, sh.T, sh.d, sh.d_ff, ws.nseg, t, ws.slots, ws.tc,
                                 ws.meta, ws.seg_count, ws.seg_idx, ws.seg_act, ws.zf, y, ws.xs, token_tiles(ws), form,
-                                (const float*)ws.gx, LOPA ? sh.sc.b : sh.sc.gate, sh.sc.up, sh.sc.down);
+                                (const float*)ws.gx, LOPA ? sh.sc.b : sh.sc.gate, sh.sc.up, sh.sc.down, alive_masks(ws));
     }
   // two workgroups a CU only where their segments stay near 64 rows: halving 8B-shaped
   // segments to 28 rows left the row tiles half empty (int8 / int4 at four tokens: 52.7 /
@@ -1312,7 +1506,7 @@ hipError_t gate_mfma(const Shape& sh, const Form& form, const float* x, const vo
   return launch_gate_kernel(kernel, g, s, x, (const float*)ws.z, static_cast<const uint4*>(gate_w), Cg,
                             static_cast<const uint4*>(w_up), Cu, sh.T, sh.d, sh.d_ff, ws.nseg, t, ws.slots, ws.tc,
                             ws.meta, ws.seg_count, ws.seg_idx, ws.seg_act, ws.zf, y, ws.xs, token_tiles(ws), form,
-                            (const float*)ws.gx, LOPA ? sh.sc.b : sh.sc.gate, sh.sc.up, sh.sc.down);
+                            (const float*)ws.gx, LOPA ? sh.sc.b : sh.sc.gate, sh.sc.up, sh.sc.down, alive_masks(ws));
 }
 
 template <class W, bool LOPA, bool DENSE, int FORM>
@@ -1355,7 +1549,8 @@ hipError_t down_mfma(const Shape& sh, const void* w_down_t, const Workspace& ws,
   while (R < ws.nseg && ((ws.nseg + R - 1) / R) * rows_per_seg > kDnSlots) ++R;
   if (((ws.nseg + R - 1) / R) * rows_per_seg > kDnSlots || S * R > INT32_MAX) return hipErrorInvalidValue;
   k_down_mfma<NT, W><<<(int)(S * R), kBlock, 0, s>>>(ws.seg_count, ws.seg_idx, ws.zf, ws.nseg, sh.d_ff, (int)R,
-                                                     ws.tc, static_cast<const uint4*>(w_down_t), C, sh.d, sh.T, y);
+                                                     ws.tc, static_cast<const uint4*>(w_down_t), C, sh.d, sh.T, y,
+                                                     reinterpret_cast<const uint2*>(alive_masks(ws)));
   return hipGetLastError();
 }
 
@@ -1391,15 +1586,19 @@ hipError_t batched_format(const Shape& sh, Gate g, bool dense, const Form& form,
 
 // The matrix-core path addresses every operand with 32-bit byte offsets below 2^31.
 // bf16 weights, and int8 / int4 codes (converted to bf16 on their way into the operand
-// tiles): rows of whole 16-byte chunks, so d (and LoPA's r) a multiple of 16 / 32.
+// tiles): rows of whole 16-byte chunks, so d (and LoPA's r) a multiple of 16 / 32.  fp32 weights
+// likewise, d and r multiples of 4, at every batch size: against the vector-ALU kernels (which keep
+// the other widths) at d 3840, d_ff 14231, r 480, 90%: 2 tokens 57.1 -> 44.5 us a call, 4 109.7 ->
+// 55.4, 16 508 -> 90.5, 64 2024 -> 205; d 512, d_ff 2000, standard gating, 3 tokens 21.2 -> 17.6.
 bool batched_ok(const Shape& sh, Gate g) {
-  if (sh.wdt < 1 || sh.wdt > 3 || sh.T < 2 || sh.T > kTokChunk) return false;
-  const int q = sh.wdt == 1 ? 8 : sh.wdt == 2 ? 16 : 32;  // elements a 16-byte chunk
+  if (sh.wdt < 0 || sh.wdt > 3 || sh.T < 2 || sh.T > kTokChunk) return false;
+  const int q = sh.wdt == 0 ? 4 : sh.wdt == 1 ? 8 : sh.wdt == 2 ? 16 : 32;  // elements a 16-byte chunk
+  const int eb = sh.wdt == 0 ? 4 : 2;                                       // bytes an element, at most
   if (sh.d % q != 0) return false;
   const int64_t lim = int64_t(1) << 31;
-  if (2 * (int64_t)sh.d_ff * sh.d >= lim || 4 * (int64_t)kTokChunk * sh.d >= lim) return false;
+  if (eb * (int64_t)sh.d_ff * sh.d >= lim || 4 * (int64_t)kTokChunk * sh.d >= lim) return false;
   if ((int64_t)segments_for(sh.d_ff, kSegGrid2) * 256 * kTokChunk >= lim) return false;
-  if (g == Gate::LoPA && (sh.r % q != 0 || 2 * (int64_t)sh.d_ff * sh.r >= lim || 2 * (int64_t)sh.r * sh.d >= lim ||
+  if (g == Gate::LoPA && (sh.r % q != 0 || eb * (int64_t)sh.d_ff * sh.r >= lim || eb * (int64_t)sh.r * sh.d >= lim ||
                           4 * (int64_t)kTokChunk * sh.d_ff >= lim))  // G x, read through a buffer
     return false;
   return true;
@@ -1413,7 +1612,10 @@ hipError_t launch_batched(const Shape& sh, Gate g, bool dense, const Form& form,
                           Workspace& ws, float* y, hipStream_t s) {
   hipError_t e = hipSuccess;
   // more than one token tile: the kernels read the tokens pre-split
-  if (sh.T > 16 && (e = split_tokens(sh, x, ws, s)) != hipSuccess) return e;
+  if (sh.T > 16 &&
+      (e = sh.wdt == 0 ? split_tokens<true>(sh, x, ws, s) : split_tokens<false>(sh, x, ws, s)) != hipSuccess)
+    return e;
+  if (sh.wdt == 0) return batched_format<WF32>(sh, g, dense, form, x, lopa_a, gate_w, w_up, w_down_t, t, ws, y, s);
   if (sh.wdt == 2) return batched_format<WI8>(sh, g, dense, form, x, lopa_a, gate_w, w_up, w_down_t, t, ws, y, s);
   if (sh.wdt == 3) return batched_format<WI4>(sh, g, dense, form, x, lopa_a, gate_w, w_up, w_down_t, t, ws, y, s);
   return batched_format<WBf16>(sh, g, dense, form, x, lopa_a, gate_w, w_up, w_down_t, t, ws, y, s);

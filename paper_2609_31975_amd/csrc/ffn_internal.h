@@ -67,11 +67,12 @@ struct Workspace {
   float* zsq;          // [r]              squares of z (single-token LoPA path with RMSNorm)
   float* gx;           // [tc][d_ff]       G x per token (LoPA with G, single-token and
                        //                  matrix-core paths; written by the z kernel)
-  uint4* zf;           // [2 batched_segments(d_ff)][ceil(tc / 16)][2][64]  zval fragments of the
-                       //                  down product, hi and lo planes of 64 lanes per fragment
-                       //                  group and token tile (matrix-core path, tc >= 2)
+  uint4* zf;           // [16 batched_segments(d_ff)][ceil(tc / 16)][16]  zval of the down product by
+                       //                  quads of union entries, token tile and token (bf16 hi and
+                       //                  lo parts, or fp32; matrix-core path, tc >= 2)
   uint4* xs;           // [2][ceil(d / 32)][ceil(tc / 16)][64]  tokens split into bf16 hi / lo
-                       //                  matrix-core fragments (tc >= kPreSplitMin, else empty)
+                       //                  matrix-core fragments, or as fp32 ones [ceil(d / 16)]...
+                       //                  (tc >= kPreSplitMin, else empty)
 };
 
 size_t workspace_layout(int T, int d, int d_ff, int r, void* base, Workspace* out);
@@ -146,7 +147,7 @@ hipError_t launch_down(const Shape& sh, bool dense, const void* w_down_t, const 
 // kernel then clears ws.zslot): fp32 / bf16 rows of the single-token kernels, r <= kFusedZMax.
 bool lopa_fuses_z(const Shape& sh, const Form& form);
 
-// Matrix-core path for batches of 2..64 tokens with bf16 weights (ffn_batched.hip):
+// Matrix-core path for batches of 2..64 tokens (ffn_batched.hip):
 // the whole call (LoPA z, gate + union + W_up, down), clearing y first.
 bool batched_ok(const Shape& sh, Gate g);
 int batched_segments(int d_ff);
