@@ -16,9 +16,9 @@ from concurrent.futures import ThreadPoolExecutor
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 SOURCES = [os.path.join(PKG, "csrc", f) for f in ("ffn_api.hip", "ffn_kernels.hip", "ffn_batched.hip",
-                                                  "ffn_lopa_approx.hip")]
+                                                  "ffn_wide.hip", "ffn_lopa_approx.hip")]
 HEADERS = [os.path.join(ROOT, "include", h) for h in ("ffn_sparse.h", "ffn_lopa_approx.h")] + \
-    [os.path.join(PKG, "csrc", f) for f in ("ffn_internal.h", "ffn_device.h")]
+    [os.path.join(PKG, "csrc", f) for f in ("ffn_internal.h", "ffn_device.h", "ffn_mfma.h")]
 LIB = os.path.join(PKG, "libffn_sparse.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

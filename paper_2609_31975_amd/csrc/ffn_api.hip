@@ -160,14 +160,27 @@ int run(const Call& c) {
   Workspace ws;
   if (c.ws_bytes < workspace_layout(c.T, c.d, c.d_ff, c.r, c.ws, &ws)) return FFN_ERR_WORKSPACE;
 
-  // tokens run in passes of up to kTokChunk; each pass is an independent FFN call
-  for (int t0 = 0; t0 < c.T; t0 += kTokChunk) {
-    Shape sh{c.T - t0 < kTokChunk ? c.T - t0 : kTokChunk, c.d, c.d_ff, c.r, (int)c.wdt, scales};
+  const Gate g = lopa ? Gate::LoPA : Gate::Standard;
+  // Tokens run in passes; each pass is an independent FFN call.  More than kTokChunk tokens take
+  // equal passes (in whole token tiles) of as many as the wide kernels have workspace for, else,
+  // and for a last pass of at most kTokChunk, passes of up to kTokChunk.
+  int per = kTokChunk;
+  const size_t head = reinterpret_cast<char*>(ws.seg_count) - static_cast<char*>(c.ws);  // meta and z slots stay
+  if (c.T > kTokChunk) {
+    const int most = wide_pass_tokens(Shape{c.T, c.d, c.d_ff, c.r, (int)c.wdt, scales}, g, form, head, c.ws_bytes);
+    if (most > 0) {
+      const int n = (c.T + most - 1) / most;
+      per = ((c.T + n - 1) / n + 15) / 16 * 16;
+    }
+  }
+  for (int t0 = 0; t0 < c.T; t0 += per) {
+    Shape sh{c.T - t0 < per ? c.T - t0 : per, c.d, c.d_ff, c.r, (int)c.wdt, scales};
     const float* x = c.x + (size_t)t0 * c.d;
     float* y = c.y + (size_t)t0 * c.d;
-    const Gate g = lopa ? Gate::LoPA : Gate::Standard;
     hipError_t e = hipSuccess;
-    if (batched_ok(sh, g)) {
+    if (sh.T > kTokChunk) {
+      e = launch_wide(sh, g, c.dense, form, x, c.lopa_a, c.gate, c.w_up, c.w_down_t, c.t, c.ws, head, y, c.stream);
+    } else if (batched_ok(sh, g)) {
       e = launch_batched(sh, g, c.dense, form, x, c.lopa_a, c.gate, c.w_up, c.w_down_t, c.t, ws, y, c.stream);
     } else {
       // z = A x: in the gate kernel where it can (its down kernel then clears the z slots)

@@ -40,14 +40,10 @@
 // reads hands every lane its 8 entries of one column.
 #include "ffn_device.h"
 #include "ffn_internal.h"
+#include "ffn_mfma.h"
 
 namespace ffn {
 namespace {
-
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef short short4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kTiles = 4;                // 16-row tiles of a gate segment
 constexpr int kSegRowsB = 16 * kTiles;   // rows per gate segment (one 64-lane ballot)
@@ -55,89 +51,6 @@ constexpr int kParts = kBlock / kWave;   // k parts of a workgroup, one per wave
 constexpr int kSegQuads = kSegRowsB / 4; // union entries go to the down kernel by quads
 constexpr int kSegGrid = 256;            // most workgroups of the gate kernel, one per CU
 constexpr int kSegGrid2 = 512;           // the same at two workgroups per CU
-
-__device__ __forceinline__ f32x4_t mfma16(bf16x8_t a, bf16x8_t b, f32x4_t c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ bf16x8_t bf8(uint4 v) { return __builtin_bit_cast(bf16x8_t, v); }
-
-// fp32 weights: the same kernels on v_mfma_f32_16x16x4_f32.  A tile chunk is then 4 fp32 (16
-// bytes, as 8 bf16 are), the tokens, z and zval stay fp32, and a k step of four chunks is four
-// products: component j of every lane's chunk in product j.  A product adds its terms one after
-// the other, so a long range in one accumulator rounds like a serial sum (a call's error against
-// 64 bits at d = 3840, d_ff = 14231, r = 480, 16 tokens: 7.9e-7, the vector-ALU kernels' 3.5e-7).
-// Every k step of the gate and W_up products is summed from zero, then into its load group's
-// sum, then into the running sum; the down product sums every group of 32 rows from zero (3.4e-7).
-template <class W>
-constexpr bool is_f32() {
-  return W::EPC == 4;
-}
-template <class W>
-constexpr int tile_elems() {  // elements of a 16-byte tile chunk
-  return is_f32<W>() ? 4 : 8;
-}
-template <class W>
-constexpr uint32_t tok_bytes() {  // bytes of a token's fp32 chunk
-  return is_f32<W>() ? 16u : 32u;
-}
-__device__ __forceinline__ f32x4_t mfma16f(float a, float b, f32x4_t c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-template <int J>
-__device__ __forceinline__ float comp(const uint4& v) {
-  return __uint_as_float(J == 0 ? v.x : J == 1 ? v.y : J == 2 ? v.z : v.w);
-}
-
-// v = hi + lo with both in bf16 (round to nearest even twice)
-__device__ __forceinline__ void split8(const float (&v)[8], bf16x8_t& hi, bf16x8_t& lo) {
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const __bf16 h = (__bf16)v[j];
-    hi[j] = h;
-    lo[j] = (__bf16)(v[j] - (float)h);
-  }
-}
-
-// Chunk j (elements 8j .. 8j + 7) of a loaded 16-byte chunk of W, as 8 bf16: the chunk
-// itself for bf16, the codes converted for int8 / int4 (exact: small integers), so that
-// quantized rows enter the same bf16 operand tiles.  The row scales are applied to the
-// products.
-template <class W, int J>
-__device__ __forceinline__ uint4 bf16_chunk(const uint4& v) {
-  if constexpr (W::EPC == 8) {
-    return v;
-  } else {
-    const uint32_t d[4] = {v.x, v.y, v.z, v.w};
-    uint32_t o[4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      float a, b;  // elements 8J + 2p and 8J + 2p + 1
-      if constexpr (W::EPC == 16) {
-        const uint32_t w = d[2 * J + (p >> 1)];
-        const int e = 2 * (p & 1);
-        a = (float)((int32_t)(w << (24 - 8 * e)) >> 24);
-        b = (float)((int32_t)(w << (16 - 8 * e)) >> 24);
-      } else {
-        const uint32_t w = d[J];
-        a = (float)((int32_t)(w << (28 - 8 * p)) >> 28);
-        b = (float)((int32_t)(w << (24 - 8 * p)) >> 28);
-      }
-      // the high halves of both (selector bytes 2, 3 of the second operand, then of the first)
-      o[p] = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
-    }
-    return make_uint4(o[0], o[1], o[2], o[3]);
-  }
-}
-// all W::EPC / 8 of them into consecutive 16-byte slots of an LDS row
-template <class W>
-__device__ __forceinline__ void put_bf16_chunks(uint4* dst, const uint4& v) {
-  dst[0] = bf16_chunk<W, 0>(v);
-  if constexpr (W::EPC >= 16) dst[1] = bf16_chunk<W, 1>(v);
-  if constexpr (W::EPC >= 32) {
-    dst[2] = bf16_chunk<W, 2>(v);
-    dst[3] = bf16_chunk<W, 3>(v);
-  }
-}
 
 // k-step range [ks0, ks1) of k part kp out of np for rows of C chunks (4 chunks a step)
 __device__ __forceinline__ void kpart(int C, int kp, int np, int* ks0, int* ks1) {
@@ -1193,11 +1106,6 @@ __device__ __forceinline__ void dn_issue(DnFrags<NT, W>& f, const DnRows<NT, W>&
                                : kOOB));
 }
 
-__device__ __forceinline__ uint2 lds_read_tr16(const char* p) {
-  const short4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4_t*)(p));
-  return __builtin_bit_cast(uint2, v);
-}
-
 template <int I>
 struct Int {
   static constexpr int value = I;
@@ -1606,6 +1514,16 @@ bool batched_ok(const Shape& sh, Gate g) {
 
 // the most segments any gate kernel of this path uses (workspace sizing)
 int batched_segments(int d_ff) { return segments_for(d_ff, kSegGrid2); }
+
+hipError_t launch_split_tokens(const Shape& sh, const float* x, const Workspace& ws, hipStream_t s) {
+  return split_tokens<false>(sh, x, ws, s);
+}
+hipError_t launch_z_tiles(const Shape& sh, const Form& form, const float* x, const void* lopa_a, const Workspace& ws,
+                          hipStream_t s) {
+  if (sh.wdt == 2) return z_mfma<WI8, 1, true>(sh, form, x, lopa_a, ws, s);
+  if (sh.wdt == 3) return z_mfma<WI4, 1, true>(sh, form, x, lopa_a, ws, s);
+  return z_mfma<WBf16, 1, true>(sh, form, x, lopa_a, ws, s);
+}
 
 hipError_t launch_batched(const Shape& sh, Gate g, bool dense, const Form& form, const float* x,
                           const void* lopa_a, const void* gate_w, const void* w_up, const void* w_down_t, float t,

@@ -1,0 +1,723 @@
+// gfx950 kernels for calls of more than 64 tokens with bf16 or int8 / int4 weights.
+//
+// A pass of the 2..64-token kernels re-reads every token for each 64 weight rows and every
+// weight row for each 64 tokens: at 200 tokens (8B shape, LoPA r = 512) four passes took 345 us,
+// each reading the weights again and 2.3 times their bytes of token fragments.  Here all tokens
+// that fit the workspace go in one pass, and every product is tiled on both sides:
+//   k_wide_gate_up  a workgroup takes up to 128 rows of the gate and a block of up to 128 tokens:
+//                   gate product, thresholds, the block's union of active rows, then the W_up
+//                   product of the union rows against the same tokens; zval by quads of entries
+//   k_wide_down     a workgroup takes 128 columns of W_down, a chunk of the segments and a block
+//                   of tokens: Y[tokens][cols] += Z[tokens][entries] D[entries][cols]
+// with k_split_tokens (the tokens as bf16 hi / lo fragment planes) and, for LoPA, k_lopa_z_mfma and
+// k_split_z (the same for z) before them.
+//
+// Both products stage both operands in LDS: eight waves, two over the rows (columns), two over the
+// tokens and two over the k steps of an iteration, a wave's tile being 64 x 64.  One iteration
+// (64 k, 48 KB) is 256 products a wave pair against 96 KB of LDS reads; a wave of 64 x 64 needs
+// three 16-byte LDS reads for eight products, which keeps the LDS (128 bytes a clock) below the
+// matrix cores' time.  The two halves of the k steps give a SIMD two waves, so that one's LDS reads
+// overlap the other's products.  Loads run through registers, two iterations ahead of their use
+// (the tokens come from L2, the weights from HBM), into two LDS buffers: one barrier an iteration.
+// The workgroups of the token blocks of one segment (or chunk) run on one XCD, so that its L2 serves
+// the weights to all but the first.
+#include "ffn_device.h"
+#include "ffn_internal.h"
+#include "ffn_mfma.h"
+
+namespace ffn {
+namespace {
+
+constexpr int kWThreads = 512;
+constexpr int kWTiles = 8;                  // token tiles (of 16) of a block
+constexpr int kWRows = 128;                 // most rows of a segment
+constexpr int kWCols = 128;                 // columns of a down workgroup
+constexpr int kWDnRows = 4096;              // most rows of a down workgroup's chunk
+constexpr int kWDnSegs = 128;               // most segments of it
+constexpr int kWDnList = kWDnRows + 3 * kWDnSegs + 64 * 5;  // packed entries, see k_wide_down
+constexpr int kXcds = 8;
+
+// Workgroup b of a grid of units x blocks: the blocks of a unit are kXcds apart, on one XCD.
+__device__ __forceinline__ void unit_of(int b, int nb, int* unit, int* blk) {
+  const int grp = b / (kXcds * nb), in = b - grp * kXcds * nb;
+  *blk = in / kXcds;
+  *unit = grp * kXcds + in % kXcds;
+}
+
+// The two k groups' sums of a wave pair (waves w and w ^ 4) meet: wave w ends with the sums of
+// f[i][j] = acc[kg N / 2 + i][j], kg = w >> 2.  buf: 8 N / 2 M 64 f32x4.
+template <int N, int M>
+__device__ __forceinline__ void join_k(const f32x4_t (&acc)[N][M], f32x4_t* buf, f32x4_t (&f)[N / 2][M]) {
+  const int lane = lane_id(), wave = uniform(threadIdx.x / kWave);
+  const bool hi = wave >= 4;
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i)
+#pragma unroll
+    for (int j = 0; j < M; ++j) buf[((wave * (N / 2) + i) * M + j) * kWave + lane] = hi ? acc[i][j] : acc[N / 2 + i][j];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i)
+#pragma unroll
+    for (int j = 0; j < M; ++j)
+      f[i][j] = (hi ? acc[N / 2 + i][j] : acc[i][j]) + buf[(((wave ^ 4) * (N / 2) + i) * M + j) * kWave + lane];
+}
+
+// Waits for the wave's loads and stores (vmcnt 0, the other counters as they are).
+__device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
+// ------------------------------------------------------------------ rows x tokens
+// LDS of one product: the rows' chunks in operand order ([k step][row tile][lane group g][row],
+// the row index xor-ed with the chunk's place in the iteration so that a row's eight chunks, which
+// neighbouring lanes write, fall on distinct banks), and the tokens' hi and lo planes as they are
+// in memory.
+struct WideStage {
+  uint4 w[2][2][kWTiles][4][16];
+  uint4 x[2][2][2][kWTiles][kWave];  // [buffer][plane][k step][token tile][lane]
+};
+
+// acc[i][j] += rows (row tile wr + 2 i) . tokens (token tile wt + 2 j) for a wave (kg, wr, wt) over
+// its half of the k steps.  roff[i]: the loaded chunk at which row (threadIdx.x / LPR + RPP i)
+// starts, or -1.  C: tile chunks (8 elements) a row; the tokens' planes start at xb, part_bytes
+// apart, tile nt0 the block's first of ntb, ntt a k step.
+template <class W, int RT>
+struct WideRows {
+  static constexpr int R8 = W::EPC / 8;            // tile chunks per loaded chunk
+  static constexpr int LPR = 8 / R8;               // loaded chunks of a row an iteration
+  static constexpr int RPP = kWThreads / LPR;      // rows a load of all threads covers
+  static constexpr int NL = (32 * RT + RPP - 1) / RPP;
+};
+
+template <class W, int RT>
+__device__ __forceinline__ void wide_product(WideStage& st, const Buf& wb, int C, const int* roff, const Buf& xb,
+                                             uint32_t part_bytes, int ntt, int nt0, int ntb, f32x4_t (&acc)[RT][4]) {
+  using S = WideRows<W, RT>;
+  const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid / kWave);
+  const int nks = (C + 3) / 4, nit = (nks + 1) / 2;
+  const int kg = wave >> 2, wr = (wave >> 1) & 1, wt = wave & 1, m = lane & 15, g = lane >> 4;
+  struct Regs {
+    uint4 w[S::NL], x[2][2];
+  };
+  const bool tile_ok = wave < ntb;
+  auto load = [&](Regs& r, int it) {
+    const int lc = tid % S::LPR, ch = it * S::LPR + lc;  // the lane's loaded chunk of the row
+    const bool cv = it < nit && ch < C / S::R8;
+#pragma unroll
+    for (int i = 0; i < S::NL; ++i) r.w[i] = ldb(wb, cv && roff[i] >= 0 ? 16u * (uint32_t)(roff[i] + ch) : kOOB);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int ks = 2 * it + k;
+      const uint32_t off =
+          tile_ok && ks < nks ? 16u * ((uint32_t)(ks * ntt + nt0 + wave) * kWave + (uint32_t)lane) : kOOB;
+      r.x[0][k] = ldb(xb, off);
+      r.x[1][k] = ldb(xb, off + part_bytes);
+    }
+  };
+  auto put = [&](const Regs& r, int b) {
+    const int lc = tid % S::LPR;
+#pragma unroll
+    for (int i = 0; i < S::NL; ++i) {
+      const int row = tid / S::LPR + S::RPP * i;
+      if (row < 32 * RT) {
+        uint4 t[S::R8];
+        put_bf16_chunks<W>(t, r.w[i]);
+#pragma unroll
+        for (int c = 0; c < S::R8; ++c) {
+          const int at = lc * S::R8 + c;  // tile chunk of the iteration
+          st.w[b][at >> 2][row >> 4][at & 3][(row & 15) ^ (2 * (at & 3) + 8 * (at >> 2))] = t[c];
+        }
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int k = 0; k < 2; ++k) st.x[b][p][k][wave][lane] = r.x[p][k];
+  };
+  auto mma = [&](int b) {
+    bf16x8_t a[RT], xh[4], xl[4];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) a[i] = bf8(st.w[b][kg][wr + 2 * i][g][m ^ (2 * g + 8 * kg)]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      xh[j] = bf8(st.x[b][0][kg][wt + 2 * j][lane]);
+      xl[j] = bf8(st.x[b][1][kg][wt + 2 * j][lane]);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < RT; ++i) acc[i][j] = mfma16(a[i], xh[j], acc[i][j]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < RT; ++i) acc[i][j] = mfma16(a[i], xl[j], acc[i][j]);
+  };
+  // Iteration it: its tile is in buffer it & 1, the next one in r1 (or r0), the one after it in
+  // flight.  A pair of iterations always runs whole (one past the end loads nothing and adds
+  // zeros), so that no load sits on a conditional path.
+  Regs r0, r1;
+  load(r0, 0);
+  load(r1, 1);
+  put(r0, 0);
+  load(r0, 2);
+  __syncthreads();
+  for (int it = 0;; it += 2) {
+    put(r1, 1);
+    load(r1, it + 3);
+    issue_barrier();
+    mma(0);
+    __syncthreads();
+    put(r0, 0);
+    load(r0, it + 4);
+    issue_barrier();
+    mma(1);
+    __syncthreads();
+    if (it + 2 >= nit) break;
+  }
+}
+
+struct WideArgs {
+  const uint4 *gate_w, *w_up;
+  const uint4 *xs, *zs;  // token planes of x and (LoPA) z
+  int Cg, Cu;            // tile chunks of a gate row, of a W_up row
+  int T, d, d_ff, nseg, qps, ntt, nb;  // qps: quads a segment has room for
+  int lopa, dense;
+  float t;
+  Form form;
+  const float* gx;                    // G x [T][d_ff] (LoPA with G)
+  const float *s_g, *s_up, *s_down;   // row scales (int8 / int4)
+  int32_t* seg_count;                 // [nb][nseg]
+  int32_t* seg_idx;                   // [nb][d_ff]
+  uint4* zf;   // zval by quads: block b's quads at uint4 16 nt0(b) nseg qps, of segment seg from quad
+               // seg qps, [quad][token tile of the block][16]
+  float* y;
+};
+__device__ __forceinline__ uint32_t plane_bytes(int C, int ntt) {
+  return 16u * (uint32_t)((C + 3) / 4) * (uint32_t)ntt * (uint32_t)kWave;
+}
+
+// Gate, union and W_up of one segment (up to 32 RT rows) for one block of tokens.  The activation
+// values wait in the segment's own part of the zval buffer ([row][token of the block], the same
+// size) for the W_up sums: they are read back before the first zval is written there.
+template <class W>
+__global__ __launch_bounds__(kWThreads) void k_wide_gate_up(WideArgs a) {
+  constexpr bool Q = is_quant<W>();
+  __shared__ union {
+    WideStage st;
+    f32x4_t join[8 * 2 * 4 * kWave];
+  } s;
+  __shared__ uint32_t s_mask[kWTiles];
+  __shared__ int s_list[kWRows];
+
+  const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid / kWave);
+  const int kg = wave >> 2, wr = (wave >> 1) & 1, wt = wave & 1, m = lane & 15, g = lane >> 4;
+  for (int j = blockIdx.x * kWThreads + tid; j < a.T * a.d; j += gridDim.x * kWThreads) a.y[j] = 0.f;
+  int seg, blk;
+  unit_of(blockIdx.x, a.nb, &seg, &blk);
+  if (seg >= a.nseg) return;  // workgroup-uniform
+  const Split tiles(a.ntt, a.nb), segs(a.d_ff, a.nseg);
+  const int nt0 = tiles.start(blk), ntb = tiles.start(blk + 1) - nt0;  // <= kWTiles
+  const int row0 = segs.start(seg), nrows = segs.start(seg + 1) - row0;  // <= kWRows
+  uint4* const zq = a.zf + ((size_t)nt0 * a.nseg + (size_t)seg * ntb) * a.qps * 16;
+  float* const act = reinterpret_cast<float*>(zq);  // [nrows][16 ntb]
+  if (tid < kWTiles) s_mask[tid] = 0u;
+
+  // the rows of a product: rows list[k], k < n, of a matrix of C chunks a row
+  auto product = [&](const uint4* mat, int C, const uint4* planes, int n, auto row_of, auto& acc) {
+    constexpr int RT = sizeof(acc) / sizeof(acc[0]);
+    using S = WideRows<W, RT>;
+    const uint32_t part = plane_bytes(C, a.ntt);
+    const int Cl = C / S::R8;
+    int roff[S::NL];
+#pragma unroll
+    for (int i = 0; i < S::NL; ++i) {
+      const int k = tid / S::LPR + S::RPP * i;
+      roff[i] = k < n ? row_of(k) * Cl : -1;
+    }
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    wide_product<W, RT>(s.st, make_buf(mat, 16u * (uint32_t)a.d_ff * (uint32_t)Cl), C, roff, make_buf(planes, 2 * part),
+                        part, a.ntt, nt0, ntb, acc);
+  };
+
+  // thresholds of the wave's half of the row tiles: activation values out, the rows that any
+  // token of the block activates into s_mask
+  auto gate = [&](auto& acc) {
+    constexpr int RT = sizeof(acc) / sizeof(acc[0]);
+    product(a.gate_w, a.Cg, a.lopa ? a.zs : a.xs, nrows, [&](int k) { return row0 + k; }, acc);
+    f32x4_t h[RT / 2][4];
+    join_k(acc, s.join, h);
+    const Buf qb = make_buf(a.s_g, 4u * (uint32_t)a.d_ff);
+    const bool has_g = a.lopa && a.form.g_idx;
+#pragma unroll
+    for (int i = 0; i < RT / 2; ++i) {
+      const int rt = wr + 2 * (kg * (RT / 2) + i);
+      uint32_t mask = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int rl = 16 * rt + 4 * g + e;
+        const bool rv = rl < nrows;
+        const float sc = Q ? __int_as_float(ldb32(qb, rv ? 4u * (uint32_t)(row0 + rl) : kOOB)) : 1.f;
+        bool any = false;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int nt = wt + 2 * j, tok = 16 * (nt0 + nt) + m;
+          const bool tv = nt < ntb && tok < a.T;
+          float hv = h[i][j][e];
+          if constexpr (Q) hv *= sc;
+          if (has_g && rv && tv) hv += a.gx[(size_t)tok * a.d_ff + row0 + rl];
+          const bool on = tv && hv > a.t;  // NaN compares false: inactive
+          any |= on;
+          if (rv && nt < ntb) act[(size_t)rl * 16 * ntb + 16 * nt + m] = on ? gate_value(a.form.act, hv - a.t) : 0.f;
+        }
+        const uint64_t b = __ballot(any && rv);
+#pragma unroll
+        for (int gg = 0; gg < 4; ++gg)
+          if ((b >> (16 * gg)) & 0xffffull) mask |= 1u << (4 * gg + e);
+      }
+      if (lane == 0 && mask) atomicOr(&s_mask[rt], mask);
+    }
+  };
+  __syncthreads();
+  if (nrows <= kWRows / 2) {
+    f32x4_t acc[2][4];
+    gate(acc);
+  } else {
+    f32x4_t acc[4][4];
+    gate(acc);
+  }
+  wait_vmem();  // the activation values are out
+  __syncthreads();
+
+  // the union, ascending
+  int cnt;
+  {
+    uint64_t mk[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int n = min(max(nrows - 64 * h, 0), 64);
+      const uint64_t valid = n == 64 ? ~0ull : (1ull << n) - 1;
+      const uint64_t v = (uint64_t)s_mask[4 * h] | ((uint64_t)s_mask[4 * h + 1] << 16) |
+                         ((uint64_t)s_mask[4 * h + 2] << 32) | ((uint64_t)s_mask[4 * h + 3] << 48);
+      mk[h] = (a.dense ? ~0ull : v) & valid;
+    }
+    const int c0 = __popcll(mk[0]);
+    cnt = uniform(c0 + __popcll(mk[1]));
+    if (tid < kWRows && ((tid < 64 ? mk[0] >> tid : mk[1] >> (tid - 64)) & 1ull)) {
+      const int rank = tid < 64 ? __popcll(mk[0] & ((1ull << tid) - 1))
+                                : c0 + __popcll(mk[1] & ((1ull << (tid - 64)) - 1));
+      s_list[rank] = tid;
+      a.seg_idx[(size_t)blk * a.d_ff + row0 + rank] = row0 + tid;
+    }
+    if (tid == 0) a.seg_count[blk * a.nseg + seg] = cnt;
+  }
+  __syncthreads();
+  if (cnt == 0) return;  // workgroup-uniform
+
+  // W_up dots of the union rows, then zval = activation value times the dot
+  auto up = [&](auto& acc) {
+    constexpr int RT = sizeof(acc) / sizeof(acc[0]);
+    product(a.w_up, a.Cu, a.xs, cnt, [&](int k) { return row0 + s_list[k]; }, acc);
+    float av[RT / 2][4][4], su[RT / 2][4], sd[RT / 2][4];
+    const Buf ubs = make_buf(a.s_up, 4u * (uint32_t)a.d_ff), dbs = make_buf(a.s_down, 4u * (uint32_t)a.d_ff);
+#pragma unroll
+    for (int i = 0; i < RT / 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int en = 16 * (wr + 2 * (kg * (RT / 2) + i)) + 4 * g + e;
+        const int rl = en < cnt ? s_list[en] : 0;
+        if constexpr (Q) {
+          const uint32_t off = en < cnt ? 4u * (uint32_t)(row0 + rl) : kOOB;
+          su[i][e] = __int_as_float(ldb32(ubs, off));
+          sd[i][e] = __int_as_float(ldb32(dbs, off));
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int nt = wt + 2 * j;
+          av[i][j][e] = en < cnt && nt < ntb ? act[(size_t)rl * 16 * ntb + 16 * nt + m] : 0.f;
+        }
+      }
+    f32x4_t v[RT / 2][4];
+    join_k(acc, s.join, v);
+    wait_vmem();
+    __syncthreads();  // every activation value has been read
+#pragma unroll
+    for (int i = 0; i < RT / 2; ++i) {
+      const int q = 4 * (wr + 2 * (kg * (RT / 2) + i)) + g;
+      if (4 * q >= cnt) continue;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int nt = wt + 2 * j;
+        if (nt >= ntb) continue;
+        uint32_t hw[2] = {0u, 0u}, lw[2] = {0u, 0u};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float vu = Q ? v[i][j][e] * su[i][e] : v[i][j][e];
+          float zz = 4 * q + e < cnt ? av[i][j][e] * up_value(a.form.silu_up, vu) : 0.f;
+          if constexpr (Q) zz *= sd[i][e];
+          const __bf16 hb = (__bf16)zz;
+          const __bf16 lb = (__bf16)(zz - (float)hb);
+          hw[e >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, hb) << (16 * (e & 1));
+          lw[e >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, lb) << (16 * (e & 1));
+        }
+        zq[((size_t)q * ntb + nt) * 16 + m] = make_uint4(hw[0], hw[1], lw[0], lw[1]);
+      }
+    }
+  };
+  if (cnt <= kWRows / 2) {
+    f32x4_t acc[2][4];
+    up(acc);
+  } else {
+    f32x4_t acc[4][4];
+    up(acc);
+  }
+}
+
+// ------------------------------------------------------------------ down projection
+// The chunk's union entries are packed by quads as in k_down_mfma, 64 entries an iteration: half of
+// them for each k group.  The rows go to LDS as they are (two pad chunks a row: the transposing
+// reads' eight rows on distinct banks), the zval quads beside them.  The k groups' sums meet in LDS,
+// then go to y with one fp32 atomic per token and column.
+template <class W>
+__global__ __launch_bounds__(kWThreads) void k_wide_down(const int32_t* __restrict__ seg_count,
+                                                         const int32_t* __restrict__ seg_idx,
+                                                         const uint4* __restrict__ zf, int nseg, int qps, int d_ff,
+                                                         int R, int ntt, int nb, const uint4* __restrict__ w_down_t,
+                                                         int C, int d, int T, float* __restrict__ y) {
+  constexpr int R8 = W::EPC / 8, LPR = kWCols / W::EPC, RPP = kWThreads / LPR, NL = (64 + RPP - 1) / RPP;
+  constexpr int PITCH = kWCols / 8 + 2;
+  __shared__ union {
+    struct {
+      uint4 w[2][64 * PITCH];
+      uint4 z[2][16][kWTiles][16];
+    } st;
+    f32x4_t join[8 * 2 * 4 * kWave];
+  } s;
+  __shared__ int s_row[kWDnList], s_zq[kWDnList / 4];
+  __shared__ int s_wquads[kWThreads / kWave], s_cnt[kWDnSegs], s_quad[kWDnSegs];
+
+  const int S = (d + kWCols - 1) / kWCols;
+  int unit, blk;
+  unit_of(blockIdx.x, nb, &unit, &blk);
+  if (unit >= S * R) return;  // workgroup-uniform
+  const int chunk = unit / S, cgrp = unit % S;
+  const Split chunks(nseg, R), segs(d_ff, nseg), tiles(ntt, nb);
+  const int nt0 = tiles.start(blk), ntb = tiles.start(blk + 1) - nt0;
+  const int seg_lo = chunks.start(chunk), seg_hi = chunks.start(chunk + 1);
+  const int nsc = seg_hi - seg_lo;  // <= kWDnSegs, guaranteed by the host
+  const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid / kWave);
+  const int kg = wave >> 2, wc = (wave >> 1) & 1, wt = wave & 1, m = lane & 15, g = lane >> 4;
+  const Buf db = make_buf(w_down_t, 16u * (uint32_t)d_ff * (uint32_t)C);
+  const Buf zb = make_buf(zf + (size_t)nt0 * nseg * qps * 16, 256u * (uint32_t)nseg * (uint32_t)qps * (uint32_t)ntb);
+
+  // the packed list (rows at most kWDnRows, guaranteed by the host)
+  const int c = tid < nsc ? seg_count[blk * nseg + seg_lo + tid] : 0;
+  const int quads = wave_inclusive_scan((c + 3) >> 2);
+  if (lane == kWave - 1) s_wquads[wave] = quads;
+  __syncthreads();
+  int qbase = 0, nquad = 0;
+#pragma unroll
+  for (int w = 0; w < kWThreads / kWave; ++w) {
+    const int v = s_wquads[w];
+    qbase += w < wave ? v : 0;
+    nquad += v;
+  }
+  nquad = uniform(nquad);
+  const int nit = (nquad + 15) / 16;
+  if (tid < nsc) {
+    s_cnt[tid] = c;
+    s_quad[tid] = qbase + quads - ((c + 3) >> 2);
+  }
+  for (int o = 4 * nquad + tid; o < 64 * (nit + 4); o += kWThreads) {
+    s_row[o] = -1;
+    if ((o & 3) == 0) s_zq[o >> 2] = -1;
+  }
+  __syncthreads();
+  {
+    // half-segments of 64 rows, a wave each, SU in flight
+    constexpr int SU = 8, WV = kWThreads / kWave;
+    const Buf ib = make_buf(seg_idx + (size_t)blk * d_ff, 4u * (uint32_t)d_ff);
+    for (int u0 = wave; u0 < 2 * nsc; u0 += WV * SU) {
+      int v[SU];
+#pragma unroll
+      for (int u = 0; u < SU; ++u) {
+        const int hs = u0 + u * WV, sg = hs >> 1, e = 64 * (hs & 1) + lane;
+        const bool ok = hs < 2 * nsc && e < s_cnt[hs < 2 * nsc ? sg : 0];
+        v[u] = ldb32(ib, ok ? 4u * (uint32_t)(segs.start(seg_lo + sg) + e) : kOOB);
+      }
+#pragma unroll
+      for (int u = 0; u < SU; ++u) {
+        const int hs = u0 + u * WV, sg = hs >> 1, e = 64 * (hs & 1) + lane;
+        if (hs < 2 * nsc && e < ((s_cnt[sg] + 3) & ~3)) {
+          const int o = 4 * s_quad[sg] + e;
+          s_row[o] = e < s_cnt[sg] ? v[u] : -1;
+          if ((e & 3) == 0) s_zq[o >> 2] = (seg_lo + sg) * qps + (e >> 2);
+        }
+      }
+    }
+  }
+  __syncthreads();
+
+  f32x4_t acc[4][4];  // [token tile wt + 2 j][16 columns 64 wc + 16 c]
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int cc = 0; cc < 4; ++cc) acc[j][cc] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  struct Regs {
+    uint4 w[NL], z[4];
+  };
+  const int lc = tid % LPR, ch = cgrp * LPR + lc;
+  const bool tile_ok = wave < ntb;
+  auto load = [&](Regs& r, int it) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int e = tid / LPR + RPP * i;
+      const int row = s_row[64 * it + (e < 64 ? e : 0)];
+      r.w[i] = ldb(db, e < 64 && row >= 0 && ch < C ? 16u * (uint32_t)(row * C + ch) : kOOB);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int q = s_zq[16 * it + 4 * j + g];
+      r.z[j] = ldb(zb, tile_ok && q >= 0 ? 16u * (((uint32_t)q * (uint32_t)ntb + (uint32_t)wave) * 16u + (uint32_t)m)
+                                         : kOOB);
+    }
+  };
+  auto put = [&](const Regs& r, int b) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int e = tid / LPR + RPP * i;
+      if (e < 64) put_bf16_chunks<W>(&s.st.w[b][e * PITCH + lc * R8], r.w[i]);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s.st.z[b][4 * j + g][wave][m] = r.z[j];
+  };
+  // The transposing reads as in k_down_mfma: 32 entries of the k group, the wave's 64 columns.
+  auto mma = [&](int b) {
+    constexpr int ROWB = 16 * PITCH;
+    const char* src = reinterpret_cast<const char*>(&s.st.w[b][32 * kg * PITCH]) +
+                      (4 * (lane >> 4) + ((lane >> 2) & 3)) * ROWB + 8 * (lane & 3) + 128 * wc;
+    bf16x8_t zh[4], zl[4], bc[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const u32x4_t q0 = __builtin_bit_cast(u32x4_t, s.st.z[b][8 * kg + g][wt + 2 * j][m]);
+      const u32x4_t q1 = __builtin_bit_cast(u32x4_t, s.st.z[b][8 * kg + 4 + g][wt + 2 * j][m]);
+      zh[j] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(q0, q1, 0, 1, 4, 5));
+      zl[j] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(q0, q1, 2, 3, 6, 7));
+    }
+#pragma unroll
+    for (int cc = 0; cc < 4; ++cc) {
+      const uint2 lo = lds_read_tr16(src + 32 * cc), hi = lds_read_tr16(src + 16 * ROWB + 32 * cc);
+      bc[cc] = bf8(make_uint4(lo.x, lo.y, hi.x, hi.y));
+    }
+#pragma unroll
+    for (int cc = 0; cc < 4; ++cc)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[j][cc] = mfma16(zh[j], bc[cc], acc[j][cc]);
+#pragma unroll
+    for (int cc = 0; cc < 4; ++cc)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[j][cc] = mfma16(zl[j], bc[cc], acc[j][cc]);
+  };
+  if (nit > 0) {
+    Regs r0, r1;
+    load(r0, 0);
+    load(r1, 1);
+    put(r0, 0);
+    load(r0, 2);
+    __syncthreads();
+    for (int it = 0;; it += 2) {
+      put(r1, 1);
+      load(r1, it + 3);
+      issue_barrier();
+      mma(0);
+      __syncthreads();
+      put(r0, 0);
+      load(r0, it + 4);
+      issue_barrier();
+      mma(1);
+      __syncthreads();
+      if (it + 2 >= nit) break;
+    }
+  }
+  f32x4_t f[2][4];
+  join_k(acc, s.join, f);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int nt = wt + 2 * (2 * kg + j);
+    if (nt >= ntb) continue;
+#pragma unroll
+    for (int cc = 0; cc < 4; ++cc) {
+      const int col = cgrp * kWCols + 64 * wc + 16 * cc + m;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int tok = 16 * (nt0 + nt) + 4 * g + e;
+        if (tok < T && col < d) unsafeAtomicAdd(y + (size_t)tok * d + col, f[j][cc][e]);
+      }
+    }
+  }
+}
+
+// LoPA: z as fragment planes like the tokens' (k_split_tokens), from its two partial copies
+// [2][tc][r].
+__global__ __launch_bounds__(kBlock) void k_split_z(const float* __restrict__ zp, int r, int T, int tc, int nks, int ntt,
+                                                    uint4* __restrict__ zs) {
+  const int n = nks * ntt * kWave, i = blockIdx.x * kBlock + threadIdx.x;
+  if (i >= n) return;
+  const int lane = i % kWave, fr = i / kWave, nt = fr % ntt, ks = fr / ntt;
+  const int tok = 16 * nt + (lane & 15), k = 32 * ks + 8 * (lane >> 4);
+  float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (tok < T && k < r) {  // r is a multiple of 8
+    const float* p = zp + (size_t)tok * r + k;
+    const float* q = p + (size_t)tc * r;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = p[e] + q[e];
+  }
+  bf16x8_t hi, lo;
+  split8(v, hi, lo);
+  zs[i] = __builtin_bit_cast(uint4, hi);
+  zs[n + i] = __builtin_bit_cast(uint4, lo);
+}
+
+// ------------------------------------------------------------------ host side
+// Rows a segment: 128, or 64 where segments of 128 would leave many compute units without a
+// workgroup (the product of half the rows re-reads the tokens twice as often).
+constexpr int kWFill = 192;
+
+struct WideLayout {
+  int nseg, qps, ntt, nb;
+  Workspace ws;  // tc, z, gx, xs of the shared kernels
+  int32_t *seg_count, *seg_idx;
+  uint4 *zs, *zf;
+};
+
+// The pass's regions in the workspace, behind the z slots (which stay as they are); returns the bytes.
+size_t wide_layout(int T, int d, int d_ff, int r, bool has_g, void* base, size_t head, WideLayout* out) {
+  WideLayout w{};
+  w.ntt = (T + 15) / 16;
+  w.nb = (w.ntt + kWTiles - 1) / kWTiles;
+  const int big = (d_ff + kWRows - 1) / kWRows;
+  const int rows = (int64_t)big * w.nb < kWFill ? kWRows / 2 : kWRows;
+  w.nseg = (d_ff + rows - 1) / rows;
+  w.qps = ((d_ff + w.nseg - 1) / w.nseg + 3) / 4;
+  size_t off = head;
+  char* b = static_cast<char*>(base);
+  auto take = [&](size_t bytes) {
+    char* p = b ? b + off : nullptr;
+    off += (bytes + 255) / 256 * 256;
+    return p;
+  };
+  w.ws.tc = T;
+  w.ws.r = r;
+  w.seg_count = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)w.nb * w.nseg));
+  w.seg_idx = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)w.nb * d_ff));
+  w.ws.xs = reinterpret_cast<uint4*>(take(sizeof(uint4) * 2 * (size_t)((d + 31) / 32) * w.ntt * kWave));
+  w.zf = reinterpret_cast<uint4*>(take(sizeof(uint4) * 16 * (size_t)w.ntt * w.nseg * w.qps));
+  if (r > 0) {
+    w.ws.z = reinterpret_cast<float*>(take(sizeof(float) * 2 * (size_t)T * r));
+    w.zs = reinterpret_cast<uint4*>(take(sizeof(uint4) * 2 * (size_t)((r + 31) / 32) * w.ntt * kWave));
+    if (has_g) w.ws.gx = reinterpret_cast<float*>(take(sizeof(float) * (size_t)T * d_ff));
+  }
+  if (out) *out = w;
+  return off;
+}
+
+template <class W>
+hipError_t wide_kernels(const Shape& sh, const WideArgs& a, const WideLayout& w, const void* w_down_t, hipStream_t s) {
+  const int units = (w.nseg + kXcds - 1) / kXcds * kXcds;
+  const hipError_t e = launch_gate_kernel_n(k_wide_gate_up<W>, units * w.nb, kWThreads, s, a);
+  if (e != hipSuccess) return e;
+  // Down grid: about one workgroup a CU, chunks of at least 512 rows (each chunk adds T d fp32
+  // atomics) and at most kWDnRows, kWDnSegs.
+  const int S = (sh.d + kWCols - 1) / kWCols;
+  int R = (256 + S * w.nb - 1) / (S * w.nb);
+  const int most = (sh.d_ff + 511) / 512;
+  if (R > most) R = most;
+  const int rows = (sh.d_ff + w.nseg - 1) / w.nseg;
+  int per = kWDnRows / rows;
+  if (per > kWDnSegs) per = kWDnSegs;
+  const int least = (w.nseg + per - 1) / per;
+  if (R < least) R = least;
+  if (R > w.nseg) R = w.nseg;
+  const int du = (S * R + kXcds - 1) / kXcds * kXcds;
+  k_wide_down<W><<<du * w.nb, kWThreads, 0, s>>>(w.seg_count, w.seg_idx, w.zf, w.nseg, w.qps, sh.d_ff, R, w.ntt, w.nb,
+                                                 static_cast<const uint4*>(w_down_t), sh.d / W::EPC, sh.d, sh.T, a.y);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// Tokens of a pass: the most (a multiple of 16, at most kWidePass) whose regions fit `bytes` of
+// workspace, or 0 if the path does not take the call: 65 tokens or more, bf16 or quantized rows
+// that the 2..64-token kernels take, and every byte offset below 2^31.
+// Passes of 64 against one pass here, 90%: 8B shape LoPA r = 512, 65 / 96 / 128 / 200 / 256 tokens
+// 118.8 / 171.7 / 199.5 / 345.6 / 398.6 -> 115.9 / 124.7 / 130.6 / 184.4 / 196.1 us; d 512, d_ff 2000,
+// 100 tokens 51.8 -> 39.2; 70B shape LoPA r = 1024, 100 tokens 639.8 -> 379.8.  65 tokens is the
+// smallest call that would need two passes of 64.
+int wide_pass_tokens(const Shape& sh, Gate g, const Form& form, size_t head, size_t bytes) {
+  if (sh.wdt < 1 || sh.wdt > 3 || sh.T <= kTokChunk) return 0;
+  Shape one = sh;
+  one.T = kTokChunk;
+  if (!batched_ok(one, g)) return 0;
+  const int64_t lim = int64_t(1) << 31;
+  const int r = g == Gate::LoPA ? sh.r : 0;
+  for (int t = kWidePass; t > kTokChunk; t -= 16) {
+    WideLayout w;
+    if (wide_layout(t, sh.d, sh.d_ff, r, form.g_idx != nullptr, nullptr, head, &w) > bytes) continue;
+    if (256 * (int64_t)w.nseg * w.qps * kWTiles >= lim || 4 * (int64_t)t * sh.d >= lim / 4 ||
+        4 * (int64_t)t * (r > 0 ? r : 1) >= lim / 4)
+      continue;
+    return t;
+  }
+  return 0;
+}
+
+hipError_t launch_wide(const Shape& sh, Gate g, bool dense, const Form& form, const float* x, const void* lopa_a,
+                       const void* gate_w, const void* w_up, const void* w_down_t, float t, void* base, size_t head,
+                       float* y, hipStream_t s) {
+  const bool lopa = g == Gate::LoPA;
+  WideLayout w;
+  wide_layout(sh.T, sh.d, sh.d_ff, lopa ? sh.r : 0, form.g_idx != nullptr, base, head, &w);
+  hipError_t e = launch_split_tokens(sh, x, w.ws, s);
+  if (e != hipSuccess) return e;
+  if (lopa) {
+    if ((e = launch_z_tiles(sh, form, x, lopa_a, w.ws, s)) != hipSuccess) return e;
+    if (form.rms_eps > 0.f &&
+        (e = launch_rms_norm(w.ws.z, 2, sh.T, sh.T, sh.r, form.rms_gain, form.rms_eps, s)) != hipSuccess)
+      return e;
+    const int nks = (sh.r + 31) / 32, n = nks * w.ntt * kWave;
+    k_split_z<<<(n + kBlock - 1) / kBlock, kBlock, 0, s>>>(w.ws.z, sh.r, sh.T, sh.T, nks, w.ntt, w.zs);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  WideArgs a{};
+  a.gate_w = static_cast<const uint4*>(gate_w);
+  a.w_up = static_cast<const uint4*>(w_up);
+  a.xs = w.ws.xs;
+  a.zs = w.zs;
+  a.Cu = sh.d / 8;
+  a.Cg = lopa ? sh.r / 8 : a.Cu;
+  a.T = sh.T;
+  a.d = sh.d;
+  a.d_ff = sh.d_ff;
+  a.nseg = w.nseg;
+  a.qps = w.qps;
+  a.ntt = w.ntt;
+  a.nb = w.nb;
+  a.lopa = lopa;
+  a.dense = dense;
+  a.t = t;
+  a.form = form;
+  a.gx = w.ws.gx;
+  a.s_g = lopa ? sh.sc.b : sh.sc.gate;
+  a.s_up = sh.sc.up;
+  a.s_down = sh.sc.down;
+  a.seg_count = w.seg_count;
+  a.seg_idx = w.seg_idx;
+  a.zf = w.zf;
+  a.y = y;
+  if (sh.wdt == 2) return wide_kernels<WI8>(sh, a, w, w_down_t, s);
+  if (sh.wdt == 3) return wide_kernels<WI4>(sh, a, w, w_down_t, s);
+  return wide_kernels<WBf16>(sh, a, w, w_down_t, s);
+}
+
+}  // namespace ffn

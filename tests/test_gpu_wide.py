@@ -1,0 +1,92 @@
+"""Calls of more than 64 tokens on the wide kernels (bf16, int8, int4 weights), against the oracle:
+edges of token tiles and blocks, of segments, of an iteration's 64 elements and of column groups."""
+import numpy as np
+import pytest
+
+from paper_2609_31975_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+BF16, I8, I4 = wl.BF16, wl.I8, wl.I4
+
+
+@pytest.fixture(scope="module")
+def gu():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a ROCm device"
+    from tests import gpu_util
+    return gpu_util
+
+
+# T, d, d_ff, r, wdt, threshold
+SHAPES = [
+    (65, 8, 3, 0, BF16, 0.0),           # one chunk, one segment of three rows, a tile of one token
+    (66, 72, 130, 8, BF16, 0.3),        # segments of 43 rows, a k step of one chunk, a rank of one
+    (80, 264, 1000, 40, BF16, 1.6),
+    (80, 136, 1000, 0, BF16, 3.0),      # small unions, some segments with none
+    (100, 1032, 999, 72, BF16, 1.6),    # an odd d_ff; 129 chunks a row; nine column groups
+    (128, 264, 2100, 0, BF16, 1.0),     # one full block
+    (129, 264, 12300, 40, BF16, 2.2),   # two blocks, segments of 128 and 127 rows, unions past 64
+    (129, 136, 12300, 0, BF16, -9.0),   # everything active
+    (200, 136, 12289, 16, BF16, 3.1),   # segments of up to 128 rows with unions of at most 64
+    (300, 264, 1000, 40, BF16, 1.6),    # several passes
+    (193, 72, 700, 0, BF16, 1.6),       # several passes, the last one small
+    (100, 272, 999, 48, I8, 1.6),
+    (130, 528, 12300, 0, I8, 2.4),
+    (100, 288, 999, 64, I4, 1.6),
+    (130, 544, 12300, 0, I4, 2.4),
+]
+
+
+@pytest.mark.parametrize("dense", [False, True], ids=["sparse", "dense"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "T%d_d%d_dff%d_r%d_w%d" % s[:5])
+def test_wide(gu, shape, dense):
+    T, d, d_ff, r, wdt, t = shape
+    inp = wl.make_inputs(601, T, d, d_ff, r=r, wdt=wdt)
+    dev = gu.DevInputs(inp)
+    y = (gu.run_gpu_q if wdt in (I8, I4) else gu.run_gpu)(dev, t, dense=dense)[0]
+    res = gu.run_oracle(inp, t, dense=dense)
+    gu.check_parity(res, y, None, None, t, BF16, dense=dense, what=str(shape))
+    # the tolerance of bf16 weights is wide: the tokens' two bf16 parts hold 2^-16 of an element
+    assert gu.rel_err(y, res.y) <= 3e-5
+
+
+@pytest.mark.parametrize("wdt", [BF16, I8], ids=["bf16", "i8"])
+@pytest.mark.parametrize("r", [0, 48], ids=["std", "lopa"])
+def test_wide_full_form(gu, wdt, r):
+    T, d, d_ff, t = 150, 272, 1500, 2.0
+    inp = wl.make_inputs(602, T, d, d_ff, r=r, wdt=wdt)
+    lopa = dict(form=wl.make_form(602, d, d_ff, r), use_g=True, rms_norm=True, use_gain=True) if r else {}
+    form = gu.Form(act=1, silu_up=True, **lopa)
+    dev = gu.DevInputs(inp)
+    y = gu.run_gpu_q(dev, t, form=form)[0] if wdt == I8 else gu.run_gpu_ex(dev, t, form)[0]
+    res = gu.run_oracle(inp, t, form=form)
+    gu.check_parity(res, y, None, None, t, BF16, what=f"full form w{wdt} r={r}")
+    assert gu.rel_err(y, res.y) <= 3e-5
+
+
+def test_wide_between_other_calls(gu):
+    """One workspace, no refill: single-token LoPA calls (whose z slots live in it) around wide ones."""
+    import torch
+    from paper_2609_31975_amd import ffn
+    d, d_ff, r, t, T = 264, 1000, 40, 1.2, 177
+    inp = wl.make_inputs(603, T, d, d_ff, r=r, wdt=BF16)
+    dev = gu.DevInputs(inp)
+    ws = ffn.alloc_workspace(T, d, d_ff, r)
+    res = gu.run_oracle(inp, t)
+    for n in (1, T, 1, 3, T, 1):
+        y = torch.full((n, d), float("nan"), device="cuda")
+        ffn.ffn_lopa_sparse_forward(dev.x[:n].contiguous(), dev.lopa_a, dev.lopa_b, dev.w_up, dev.w_down_t, t, y, ws)
+        assert gu.rel_err(y.cpu().numpy(), res.y[:n]) <= 3e-5, n
+
+
+def test_wide_without_a_workspace_argument(gu):
+    import torch
+    from paper_2609_31975_amd import ffn
+    d, d_ff, t, T = 264, 1000, 1.2, 100
+    inp = wl.make_inputs(604, T, d, d_ff, wdt=BF16)
+    dev = gu.DevInputs(inp)
+    y = torch.full((T, d), float("nan"), device="cuda")
+    ffn.ffn_sparse_forward_noalloc(dev.x, dev.w_gate, dev.w_up, dev.w_down_t, t, y)
+    assert gu.rel_err(y.cpu().numpy(), gu.run_oracle(inp, t).y) <= 3e-5
+    assert np.isfinite(y.cpu().numpy()).all()
