@@ -1518,13 +1518,6 @@ int batched_segments(int d_ff) { return segments_for(d_ff, kSegGrid2); }
 hipError_t launch_split_tokens(const Shape& sh, const float* x, const Workspace& ws, hipStream_t s) {
   return split_tokens<false>(sh, x, ws, s);
 }
-hipError_t launch_z_tiles(const Shape& sh, const Form& form, const float* x, const void* lopa_a, const Workspace& ws,
-                          hipStream_t s) {
-  if (sh.wdt == 2) return z_mfma<WI8, 1, true>(sh, form, x, lopa_a, ws, s);
-  if (sh.wdt == 3) return z_mfma<WI4, 1, true>(sh, form, x, lopa_a, ws, s);
-  return z_mfma<WBf16, 1, true>(sh, form, x, lopa_a, ws, s);
-}
-
 hipError_t launch_batched(const Shape& sh, Gate g, bool dense, const Form& form, const float* x,
                           const void* lopa_a, const void* gate_w, const void* w_up, const void* w_down_t, float t,
                           Workspace& ws, float* y, hipStream_t s) {

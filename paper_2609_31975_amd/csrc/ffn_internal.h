@@ -156,11 +156,8 @@ hipError_t launch_batched(const Shape& sh, Gate g, bool dense, const Form& form,
                           const void* lopa_a, const void* gate_w, const void* w_up, const void* w_down_t, float t,
                           Workspace& ws, float* y, hipStream_t s);
 
-// The token and z kernels of that path for tokens beyond one pass of it (ffn_wide.hip): the tokens'
-// bf16 hi / lo fragment planes into ws.xs, and z = A x from them into ws.z (bf16 and quantized A).
+// The tokens' bf16 hi / lo fragment planes into ws.xs.
 hipError_t launch_split_tokens(const Shape& sh, const float* x, const Workspace& ws, hipStream_t s);
-hipError_t launch_z_tiles(const Shape& sh, const Form& form, const float* x, const void* lopa_a, const Workspace& ws,
-                          hipStream_t s);
 
 // Calls of more than kTokChunk tokens (ffn_wide.hip): tokens of a pass (0: the path does not take the
 // call), and a pass of sh.T of them.  Its regions start `head` bytes into the workspace of `bytes`.

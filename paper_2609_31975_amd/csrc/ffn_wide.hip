@@ -9,16 +9,19 @@
 //                   product of the union rows against the same tokens; zval by quads of entries
 //   k_wide_down     a workgroup takes 128 columns of W_down, a chunk of the segments and a block
 //                   of tokens: Y[tokens][cols] += Z[tokens][entries] D[entries][cols]
-// with k_split_tokens (the tokens as bf16 hi / lo fragment planes) and, for LoPA, k_lopa_z_mfma and
-// k_split_z (the same for z) before them.
+// with k_split_tokens (the tokens as bf16 hi / lo fragment planes) and, for LoPA, k_wide_z (z = A x as
+// partial copies) and k_split_z (the same planes for z) before them.
 //
 // Both products stage both operands in LDS: eight waves, two over the rows (columns), two over the
 // tokens and two over the k steps of an iteration, a wave's tile being 64 x 64.  One iteration
 // (64 k, 48 KB) is 256 products a wave pair against 96 KB of LDS reads; a wave of 64 x 64 needs
-// three 16-byte LDS reads for eight products, which keeps the LDS (128 bytes a clock) below the
-// matrix cores' time.  The two halves of the k steps give a SIMD two waves, so that one's LDS reads
-// overlap the other's products.  Loads run through registers, two iterations ahead of their use
-// (the tokens come from L2, the weights from HBM), into two LDS buffers: one barrier an iteration.
+// three 16-byte LDS reads for eight products, which keeps the LDS (128 bytes a clock) near the
+// matrix cores' time.  Loads run through registers into two LDS buffers, with one barrier an
+// iteration; operands are read from LDS an iteration ahead of their products and between them (see
+// wide_product).  At 200 tokens (8B shape) k_wide_gate_up takes 82 us: 49 us with the products alone,
+// 65 with their LDS work and no loads, 91 with the weights requested four iterations ahead of their
+// products instead of six, 88 with the LDS reads of an iteration in front of its products;
+// k_wide_down 68, 75 and 81 us.
 // The workgroups of the token blocks of one segment (or chunk) run on one XCD, so that its L2 serves
 // the weights to all but the first.
 #include "ffn_device.h"
@@ -31,10 +34,12 @@ namespace {
 constexpr int kWThreads = 512;
 constexpr int kWTiles = 8;                  // token tiles (of 16) of a block
 constexpr int kWRows = 128;                 // most rows of a segment
+constexpr int kZRows = 64;                  // rows of A of a workgroup
 constexpr int kWCols = 128;                 // columns of a down workgroup
 constexpr int kWDnRows = 4096;              // most rows of a down workgroup's chunk
 constexpr int kWDnSegs = 128;               // most segments of it
-constexpr int kWDnList = kWDnRows + 3 * kWDnSegs + 64 * 5;  // packed entries, see k_wide_down
+constexpr int kWDnPad = 10;  // iterations past the last one that the down loop looks at
+constexpr int kWDnList = kWDnRows + 3 * kWDnSegs + 64 * (kWDnPad + 1);  // packed entries, see k_wide_down
 constexpr int kXcds = 8;
 
 // Workgroup b of a grid of units x blocks: the blocks of a unit are kXcds apart, on one XCD.
@@ -78,7 +83,8 @@ struct WideStage {
 // acc[i][j] += rows (row tile wr + 2 i) . tokens (token tile wt + 2 j) for a wave (kg, wr, wt) over
 // its half of the k steps.  roff[i]: the loaded chunk at which row (threadIdx.x / LPR + RPP i)
 // starts, or -1.  C: tile chunks (8 elements) a row; the tokens' planes start at xb, part_bytes
-// apart, tile nt0 the block's first of ntb, ntt a k step.
+// apart, tile nt0 the block's first of ntb, ntt a k step.  Iterations it0 .. it1 - 1 (two k steps
+// each) are summed.
 template <class W, int RT>
 struct WideRows {
   static constexpr int R8 = W::EPC / 8;            // tile chunks per loaded chunk
@@ -89,30 +95,38 @@ struct WideRows {
 
 template <class W, int RT>
 __device__ __forceinline__ void wide_product(WideStage& st, const Buf& wb, int C, const int* roff, const Buf& xb,
-                                             uint32_t part_bytes, int ntt, int nt0, int ntb, f32x4_t (&acc)[RT][4]) {
+                                             uint32_t part_bytes, int ntt, int nt0, int ntb, int it0, int it1,
+                                             f32x4_t (&acc)[RT][4]) {
   using S = WideRows<W, RT>;
   const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid / kWave);
-  const int nks = (C + 3) / 4, nit = (nks + 1) / 2;
+  const int nks = (C + 3) / 4, nit = it1 - it0;
   const int kg = wave >> 2, wr = (wave >> 1) & 1, wt = wave & 1, m = lane & 15, g = lane >> 4;
-  struct Regs {
-    uint4 w[S::NL], x[2][2];
+  struct RegsW {
+    uint4 w[S::NL];
+  };
+  struct RegsX {
+    uint4 x[2][2];  // [plane][k step]
   };
   const bool tile_ok = wave < ntb;
-  auto load = [&](Regs& r, int it) {
-    const int lc = tid % S::LPR, ch = it * S::LPR + lc;  // the lane's loaded chunk of the row
-    const bool cv = it < nit && ch < C / S::R8;
+  auto load_w = [&](RegsW& r, int t) {
+    const int it = it0 + t, lc = tid % S::LPR, ch = it * S::LPR + lc;  // the lane's loaded chunk of the row
+    const bool cv = it < it1 && ch < C / S::R8;
 #pragma unroll
     for (int i = 0; i < S::NL; ++i) r.w[i] = ldb(wb, cv && roff[i] >= 0 ? 16u * (uint32_t)(roff[i] + ch) : kOOB);
+  };
+  auto load_x = [&](RegsX& r, int t) {
+    const int it = it0 + t;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       const int ks = 2 * it + k;
-      const uint32_t off =
-          tile_ok && ks < nks ? 16u * ((uint32_t)(ks * ntt + nt0 + wave) * kWave + (uint32_t)lane) : kOOB;
+      const uint32_t off = tile_ok && it < it1 && ks < nks
+                               ? 16u * ((uint32_t)(ks * ntt + nt0 + wave) * kWave + (uint32_t)lane)
+                               : kOOB;
       r.x[0][k] = ldb(xb, off);
       r.x[1][k] = ldb(xb, off + part_bytes);
     }
   };
-  auto put = [&](const Regs& r, int b) {
+  auto put_w = [&](const RegsW& r, int b) {
     const int lc = tid % S::LPR;
 #pragma unroll
     for (int i = 0; i < S::NL; ++i) {
@@ -127,50 +141,69 @@ __device__ __forceinline__ void wide_product(WideStage& st, const Buf& wb, int C
         }
       }
     }
-#pragma unroll
-    for (int p = 0; p < 2; ++p)
-#pragma unroll
-      for (int k = 0; k < 2; ++k) st.x[b][p][k][wave][lane] = r.x[p][k];
   };
-  auto mma = [&](int b) {
-    bf16x8_t a[RT], xh[4], xl[4];
+  auto put_x = [&](const RegsX& r, int b, int p) {
 #pragma unroll
-    for (int i = 0; i < RT; ++i) a[i] = bf8(st.w[b][kg][wr + 2 * i][g][m ^ (2 * g + 8 * kg)]);
+    for (int k = 0; k < 2; ++k) st.x[b][p][k][wave][lane] = r.x[p][k];
+  };
+  // operands of the wave's k step of the tile in buffer b
+  auto read_a = [&](int b, int i) { return bf8(st.w[b][kg][wr + 2 * i][g][m ^ (2 * g + 8 * kg)]); };
+  auto read_x = [&](int b, int p, int j) { return bf8(st.x[b][p][kg][wt + 2 * j][lane]); };
+  // Iteration it multiplies tile it, whose operands are in registers already, while it reads those
+  // of tile it + 1 from the other buffer, writes tile it + 2 over tile it's and requests the tokens
+  // of tile it + 4 (from L2) and the weights of tile it + 6 (from HBM).  The barrier that ends an
+  // iteration also ends its LDS reads, so two buffers do.  The LDS work is spread between the
+  // products of the four token tiles, and a token tile's operands are read into the registers that
+  // its products have just released.  Four iterations always run (those past the end load nothing
+  // and add zeros), so that no load sits on a conditional path.
+  RegsW w0, w1, w2, w3;
+  RegsX x0, x1;
+  bf16x8_t a0[RT], a1[RT], xh[4], xl[4];
+  load_w(w0, 0), load_x(x0, 0);
+  load_w(w1, 1), load_x(x1, 1);
+  load_w(w2, 2), load_w(w3, 3);
+  put_w(w0, 0), put_x(x0, 0, 0), put_x(x0, 0, 1);
+  load_w(w0, 4), load_x(x0, 2);
+  put_w(w1, 1), put_x(x1, 1, 0), put_x(x1, 1, 1);
+  load_w(w1, 5), load_x(x1, 3);
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < RT; ++i) a0[i] = read_a(0, i);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    xh[j] = read_x(0, 0, j);
+    xl[j] = read_x(0, 1, j);
+  }
+  __syncthreads();
+  auto step = [&](const bf16x8_t (&a)[RT], bf16x8_t (&an)[RT], RegsW& w, RegsX& x, int b, int t) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      xh[j] = bf8(st.x[b][0][kg][wt + 2 * j][lane]);
-      xl[j] = bf8(st.x[b][1][kg][wt + 2 * j][lane]);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
+      if (j < RT) an[j] = read_a(b ^ 1, j);
 #pragma unroll
       for (int i = 0; i < RT; ++i) acc[i][j] = mfma16(a[i], xh[j], acc[i][j]);
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
       for (int i = 0; i < RT; ++i) acc[i][j] = mfma16(a[i], xl[j], acc[i][j]);
+      xh[j] = read_x(b ^ 1, 0, j);
+      xl[j] = read_x(b ^ 1, 1, j);
+      if (j == 0) {
+        put_w(w, b);
+        load_w(w, t + 6);
+      }
+      if (j == 1) put_x(x, b, 0);
+      if (j == 2) {
+        put_x(x, b, 1);
+        load_x(x, t + 4);
+      }
+      issue_barrier();
+    }
+    __syncthreads();
   };
-  // Iteration it: its tile is in buffer it & 1, the next one in r1 (or r0), the one after it in
-  // flight.  A pair of iterations always runs whole (one past the end loads nothing and adds
-  // zeros), so that no load sits on a conditional path.
-  Regs r0, r1;
-  load(r0, 0);
-  load(r1, 1);
-  put(r0, 0);
-  load(r0, 2);
-  __syncthreads();
-  for (int it = 0;; it += 2) {
-    put(r1, 1);
-    load(r1, it + 3);
-    issue_barrier();
-    mma(0);
-    __syncthreads();
-    put(r0, 0);
-    load(r0, it + 4);
-    issue_barrier();
-    mma(1);
-    __syncthreads();
-    if (it + 2 >= nit) break;
+  for (int t = 0;; t += 4) {
+    step(a0, a1, w2, x0, 0, t);
+    step(a1, a0, w3, x1, 1, t + 1);
+    step(a0, a1, w0, x0, 0, t + 2);
+    step(a1, a0, w1, x1, 1, t + 3);
+    if (t + 4 >= nit) break;
   }
 }
 
@@ -190,6 +223,7 @@ struct WideArgs {
                // seg qps, [quad][token tile of the block][16]
   float* y;
 };
+__host__ __device__ __forceinline__ int wide_iterations(int C) { return (C + 7) / 8; }
 __device__ __forceinline__ uint32_t plane_bytes(int C, int ntt) {
   return 16u * (uint32_t)((C + 3) / 4) * (uint32_t)ntt * (uint32_t)kWave;
 }
@@ -237,7 +271,7 @@ __global__ __launch_bounds__(kWThreads) void k_wide_gate_up(WideArgs a) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     wide_product<W, RT>(s.st, make_buf(mat, 16u * (uint32_t)a.d_ff * (uint32_t)Cl), C, roff, make_buf(planes, 2 * part),
-                        part, a.ntt, nt0, ntb, acc);
+                        part, a.ntt, nt0, ntb, 0, wide_iterations(C), acc);
   };
 
   // thresholds of the wave's half of the row tiles: activation values out, the rows that any
@@ -389,7 +423,7 @@ __global__ __launch_bounds__(kWThreads) void k_wide_down(const int32_t* __restri
   __shared__ union {
     struct {
       uint4 w[2][64 * PITCH];
-      uint4 z[2][16][kWTiles][16];
+      uint4 z[2][2][2][kWTiles][kWave];  // [buffer][k group][hi, lo][token tile][lane]
     } st;
     f32x4_t join[8 * 2 * 4 * kWave];
   } s;
@@ -428,7 +462,7 @@ __global__ __launch_bounds__(kWThreads) void k_wide_down(const int32_t* __restri
     s_cnt[tid] = c;
     s_quad[tid] = qbase + quads - ((c + 3) >> 2);
   }
-  for (int o = 4 * nquad + tid; o < 64 * (nit + 4); o += kWThreads) {
+  for (int o = 4 * nquad + tid; o < 64 * (nit + kWDnPad); o += kWThreads) {
     s_row[o] = -1;
     if ((o & 3) == 0) s_zq[o >> 2] = -1;
   }
@@ -464,80 +498,125 @@ __global__ __launch_bounds__(kWThreads) void k_wide_down(const int32_t* __restri
 #pragma unroll
     for (int cc = 0; cc < 4; ++cc) acc[j][cc] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  struct Regs {
-    uint4 w[NL], z[4];
+  struct RegsW {
+    uint4 w[NL];
+  };
+  struct RegsZ {
+    u32x4_t z[4];
+  };
+  struct Place {  // list entries of a load
+    int row[NL], zq[4];
   };
   const int lc = tid % LPR, ch = cgrp * LPR + lc;
   const bool tile_ok = wave < ntb;
-  auto load = [&](Regs& r, int it) {
+  auto rows = [&](Place& a, int it) {
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       const int e = tid / LPR + RPP * i;
-      const int row = s_row[64 * it + (e < 64 ? e : 0)];
-      r.w[i] = ldb(db, e < 64 && row >= 0 && ch < C ? 16u * (uint32_t)(row * C + ch) : kOOB);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int q = s_zq[16 * it + 4 * j + g];
-      r.z[j] = ldb(zb, tile_ok && q >= 0 ? 16u * (((uint32_t)q * (uint32_t)ntb + (uint32_t)wave) * 16u + (uint32_t)m)
-                                         : kOOB);
+      a.row[i] = s_row[64 * it + (e < 64 ? e : 0)];
     }
   };
-  auto put = [&](const Regs& r, int b) {
+  auto zqs = [&](Place& a, int it) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) a.zq[j] = s_zq[16 * it + 4 * j + g];
+  };
+  auto load_w = [&](RegsW& r, const Place& a) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i)
+      r.w[i] = ldb(db, tid / LPR + RPP * i < 64 && a.row[i] >= 0 && ch < C ? 16u * (uint32_t)(a.row[i] * C + ch) : kOOB);
+  };
+  auto load_z = [&](RegsZ& r, const Place& a) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      r.z[j] = __builtin_bit_cast(
+          u32x4_t, ldb(zb, tile_ok && a.zq[j] >= 0
+                               ? 16u * (((uint32_t)a.zq[j] * (uint32_t)ntb + (uint32_t)wave) * 16u + (uint32_t)m)
+                               : kOOB));
+  };
+  auto put_w = [&](const RegsW& r, int b) {
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       const int e = tid / LPR + RPP * i;
       if (e < 64) put_bf16_chunks<W>(&s.st.w[b][e * PITCH + lc * R8], r.w[i]);
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) s.st.z[b][4 * j + g][wave][m] = r.z[j];
   };
-  // The transposing reads as in k_down_mfma: 32 entries of the k group, the wave's 64 columns.
-  auto mma = [&](int b) {
+  // the quads 4 g and 16 + 4 g of k group k's 32 entries as one hi and one lo operand
+  auto put_z = [&](const RegsZ& r, int b, int k) {
+    s.st.z[b][k][0][wave][lane] =
+        __builtin_bit_cast(uint4, __builtin_shufflevector(r.z[2 * k], r.z[2 * k + 1], 0, 1, 4, 5));
+    s.st.z[b][k][1][wave][lane] =
+        __builtin_bit_cast(uint4, __builtin_shufflevector(r.z[2 * k], r.z[2 * k + 1], 2, 3, 6, 7));
+  };
+  // The transposing reads as in k_down_mfma: 32 entries of the k group, 16 of the wave's 64 columns.
+  auto read_d = [&](int b, int cc) {
     constexpr int ROWB = 16 * PITCH;
     const char* src = reinterpret_cast<const char*>(&s.st.w[b][32 * kg * PITCH]) +
-                      (4 * (lane >> 4) + ((lane >> 2) & 3)) * ROWB + 8 * (lane & 3) + 128 * wc;
-    bf16x8_t zh[4], zl[4], bc[4];
+                      (4 * (lane >> 4) + ((lane >> 2) & 3)) * ROWB + 8 * (lane & 3) + 128 * wc + 32 * cc;
+    const uint2 lo = lds_read_tr16(src), hi = lds_read_tr16(src + 16 * ROWB);
+    return bf8(make_uint4(lo.x, lo.y, hi.x, hi.y));
+  };
+  auto read_z = [&](int b, int p, int j) { return bf8(s.st.z[b][kg][p][wt + 2 * j][lane]); };
+  if (nit > 0) {  // the loop of wide_product, the list entries read one iteration ahead of their loads
+    RegsW w0, w1, w2, w3;
+    RegsZ z0, z1;
+    bf16x8_t d0[4], d1[4], zh[4], zl[4];
+    Place a;
+    rows(a, 0), zqs(a, 0);
+    load_w(w0, a), load_z(z0, a);
+    rows(a, 1), zqs(a, 1);
+    load_w(w1, a), load_z(z1, a);
+    rows(a, 2);
+    load_w(w2, a);
+    rows(a, 3);
+    load_w(w3, a);
+    rows(a, 4), zqs(a, 2);
+    put_w(w0, 0), put_z(z0, 0, 0), put_z(z0, 0, 1);
+    load_w(w0, a), load_z(z0, a);
+    rows(a, 5), zqs(a, 3);
+    put_w(w1, 1), put_z(z1, 1, 0), put_z(z1, 1, 1);
+    load_w(w1, a), load_z(z1, a);
+    rows(a, 6), zqs(a, 4);
+    __syncthreads();
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const u32x4_t q0 = __builtin_bit_cast(u32x4_t, s.st.z[b][8 * kg + g][wt + 2 * j][m]);
-      const u32x4_t q1 = __builtin_bit_cast(u32x4_t, s.st.z[b][8 * kg + 4 + g][wt + 2 * j][m]);
-      zh[j] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(q0, q1, 0, 1, 4, 5));
-      zl[j] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(q0, q1, 2, 3, 6, 7));
+      d0[j] = read_d(0, j);
+      zh[j] = read_z(0, 0, j);
+      zl[j] = read_z(0, 1, j);
     }
-#pragma unroll
-    for (int cc = 0; cc < 4; ++cc) {
-      const uint2 lo = lds_read_tr16(src + 32 * cc), hi = lds_read_tr16(src + 16 * ROWB + 32 * cc);
-      bc[cc] = bf8(make_uint4(lo.x, lo.y, hi.x, hi.y));
-    }
-#pragma unroll
-    for (int cc = 0; cc < 4; ++cc)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j][cc] = mfma16(zh[j], bc[cc], acc[j][cc]);
-#pragma unroll
-    for (int cc = 0; cc < 4; ++cc)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j][cc] = mfma16(zl[j], bc[cc], acc[j][cc]);
-  };
-  if (nit > 0) {
-    Regs r0, r1;
-    load(r0, 0);
-    load(r1, 1);
-    put(r0, 0);
-    load(r0, 2);
     __syncthreads();
-    for (int it = 0;; it += 2) {
-      put(r1, 1);
-      load(r1, it + 3);
-      issue_barrier();
-      mma(0);
+    auto step = [&](const bf16x8_t (&dc)[4], bf16x8_t (&dn)[4], RegsW& w, RegsZ& z, int b, int t) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        dn[j] = read_d(b ^ 1, j);
+#pragma unroll
+        for (int cc = 0; cc < 4; ++cc) acc[j][cc] = mfma16(zh[j], dc[cc], acc[j][cc]);
+#pragma unroll
+        for (int cc = 0; cc < 4; ++cc) acc[j][cc] = mfma16(zl[j], dc[cc], acc[j][cc]);
+        zh[j] = read_z(b ^ 1, 0, j);
+        zl[j] = read_z(b ^ 1, 1, j);
+        if (j == 0) {
+          put_w(w, b);
+          load_w(w, a);
+        }
+        if (j == 1) put_z(z, b, 0);
+        if (j == 2) {
+          put_z(z, b, 1);
+          load_z(z, a);
+        }
+        if (j == 3) {
+          rows(a, t + 7);
+          zqs(a, t + 5);
+        }
+        issue_barrier();
+      }
       __syncthreads();
-      put(r0, 0);
-      load(r0, it + 4);
-      issue_barrier();
-      mma(1);
-      __syncthreads();
-      if (it + 2 >= nit) break;
+    };
+    for (int t = 0;; t += 4) {
+      step(d0, d1, w2, z0, 0, t);
+      step(d1, d0, w3, z1, 1, t + 1);
+      step(d0, d1, w0, z0, 0, t + 2);
+      step(d1, d0, w1, z1, 1, t + 3);
+      if (t + 4 >= nit) break;
     }
   }
   f32x4_t f[2][4];
@@ -558,10 +637,66 @@ __global__ __launch_bounds__(kWThreads) void k_wide_down(const int32_t* __restri
   }
 }
 
-// LoPA: z as fragment planes like the tokens' (k_split_tokens), from its two partial copies
-// [2][tc][r].
-__global__ __launch_bounds__(kBlock) void k_split_z(const float* __restrict__ zp, int r, int T, int tc, int nks, int ntt,
-                                                    uint4* __restrict__ zs) {
+// ------------------------------------------------------------------ LoPA z = A x
+// Workgroup (rows 64 u .. of A, block of tokens, part p of the iterations): partial copy p of z,
+// zp[p][T][r].  The parts spread the few rows of A over the chip (r = 512, 200 tokens: 16 units, 16
+// parts of four iterations each: 9.4 us; 19.6 on the batch kernels' grid of 16-row
+// tiles, each with workgroups for every token tile); k_split_z adds them.
+template <class W>
+__global__ __launch_bounds__(kWThreads) void k_wide_z(const uint4* __restrict__ A, const uint4* __restrict__ xs, int C,
+                                                      int T, int r, int ntt, int nb, int P, float* __restrict__ zp,
+                                                      const float* __restrict__ s_a, GWork gw) {
+  if (g_precompute(gw)) return;
+  __shared__ union {
+    WideStage st;
+    f32x4_t join[8 * 2 * 4 * kWave];
+  } s;
+  const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid / kWave);
+  const int kg = wave >> 2, wr = (wave >> 1) & 1, wt = wave & 1, m = lane & 15, g = lane >> 4;
+  const int p = blockIdx.x % P, ub = blockIdx.x / P, blk = ub % nb, row0 = ub / nb * kZRows;
+  const Split tiles(ntt, nb), its(wide_iterations(C), P);
+  const int nt0 = tiles.start(blk), ntb = tiles.start(blk + 1) - nt0;
+  const int n = min(kZRows, r - row0);
+  const uint32_t part = plane_bytes(C, ntt);
+  constexpr int RT = kZRows / 32;
+  using S = WideRows<W, RT>;
+  const int Cl = C / S::R8;
+  int roff[S::NL];
+#pragma unroll
+  for (int i = 0; i < S::NL; ++i) {
+    const int k = tid / S::LPR + S::RPP * i;
+    roff[i] = k < n ? (row0 + k) * Cl : -1;
+  }
+  f32x4_t acc[RT][4];
+#pragma unroll
+  for (int i = 0; i < RT; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  wide_product<W, RT>(s.st, make_buf(A, 16u * (uint32_t)r * (uint32_t)Cl), C, roff, make_buf(xs, 2 * part), part, ntt,
+                      nt0, ntb, its.start(p), its.start(p + 1), acc);
+  f32x4_t f[RT / 2][4];
+  join_k(acc, s.join, f);
+#pragma unroll
+  for (int i = 0; i < RT / 2; ++i) {
+    const int kl = 16 * (wr + 2 * (kg * (RT / 2) + i)) + 4 * g, k = row0 + kl;
+    if (kl >= n) continue;  // r is a multiple of 8: four rows or none
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int tok = 16 * (nt0 + wt + 2 * j) + m;
+      f32x4_t v = f[i][j];
+      if constexpr (is_quant<W>()) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] *= s_a[k + e];
+      }
+      if (wt + 2 * j < ntb && tok < T) *reinterpret_cast<f32x4_t*>(zp + ((size_t)p * T + tok) * r + k) = v;
+    }
+  }
+}
+
+// z as fragment planes like the tokens' (k_split_tokens), from its `copies` partial copies
+// [copies][T][r], added in order.
+__global__ __launch_bounds__(kBlock) void k_split_z(const float* __restrict__ zp, int copies, int r, int T, int nks,
+                                                    int ntt, uint4* __restrict__ zs) {
   const int n = nks * ntt * kWave, i = blockIdx.x * kBlock + threadIdx.x;
   if (i >= n) return;
   const int lane = i % kWave, fr = i / kWave, nt = fr % ntt, ks = fr / ntt;
@@ -569,9 +704,11 @@ __global__ __launch_bounds__(kBlock) void k_split_z(const float* __restrict__ zp
   float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (tok < T && k < r) {  // r is a multiple of 8
     const float* p = zp + (size_t)tok * r + k;
-    const float* q = p + (size_t)tc * r;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = p[e] + q[e];
+#pragma unroll 4
+    for (int c = 0; c < copies; ++c, p += (size_t)T * r) {
+      const float4 a = reinterpret_cast<const float4*>(p)[0], b = reinterpret_cast<const float4*>(p)[1];
+      v[0] += a.x, v[1] += a.y, v[2] += a.z, v[3] += a.w, v[4] += b.x, v[5] += b.y, v[6] += b.z, v[7] += b.w;
+    }
   }
   bf16x8_t hi, lo;
   split8(v, hi, lo);
@@ -586,6 +723,7 @@ constexpr int kWFill = 192;
 
 struct WideLayout {
   int nseg, qps, ntt, nb;
+  int zparts;    // partial copies of z there is room for
   Workspace ws;  // tc, z, gx, xs of the shared kernels
   int32_t *seg_count, *seg_idx;
   uint4 *zs, *zf;
@@ -614,12 +752,37 @@ size_t wide_layout(int T, int d, int d_ff, int r, bool has_g, void* base, size_t
   w.ws.xs = reinterpret_cast<uint4*>(take(sizeof(uint4) * 2 * (size_t)((d + 31) / 32) * w.ntt * kWave));
   w.zf = reinterpret_cast<uint4*>(take(sizeof(uint4) * 16 * (size_t)w.ntt * w.nseg * w.qps));
   if (r > 0) {
-    w.ws.z = reinterpret_cast<float*>(take(sizeof(float) * 2 * (size_t)T * r));
+    // the partial copies of z lie where zval goes later; a copy of its own where not even two fit there
+    w.zparts = (int)(16 * (size_t)w.ntt * w.nseg * w.qps * sizeof(uint4) / (sizeof(float) * (size_t)T * r));
+    w.ws.z = reinterpret_cast<float*>(w.zf);
+    if (w.zparts < 2) {
+      w.zparts = 1;
+      w.ws.z = reinterpret_cast<float*>(take(sizeof(float) * (size_t)T * r));
+    }
     w.zs = reinterpret_cast<uint4*>(take(sizeof(uint4) * 2 * (size_t)((r + 31) / 32) * w.ntt * kWave));
     if (has_g) w.ws.gx = reinterpret_cast<float*>(take(sizeof(float) * (size_t)T * d_ff));
   }
   if (out) *out = w;
   return off;
+}
+
+// z's partial copies, `*parts` of them: about one workgroup a CU, at least four iterations each.
+template <class W>
+hipError_t wide_z(const Shape& sh, const Form& form, const float* x, const void* lopa_a, const WideLayout& w, int* parts,
+                  hipStream_t s) {
+  const int C = sh.d / 8, units = (sh.r + kZRows - 1) / kZRows * w.nb;
+  int P = (256 + units - 1) / units;
+  const int most = wide_iterations(C) / 4;
+  if (P > most) P = most;
+  if (P > w.zparts) P = w.zparts;
+  if (P < 1) P = 1;
+  *parts = P;
+  const int grid = units * P;
+  const GWork gw{form, x, w.ws.gx, sh.T, sh.d, sh.d_ff, grid};
+  const int extra = form.g_idx ? (g_items(sh.d_ff, sh.T) + kWThreads - 1) / kWThreads : 0;
+  k_wide_z<W><<<grid + extra, kWThreads, 0, s>>>(static_cast<const uint4*>(lopa_a), w.ws.xs, C, sh.T, sh.r, w.ntt, w.nb, P,
+                                                 w.ws.z, sh.sc.a, gw);
+  return hipGetLastError();
 }
 
 template <class W>
@@ -651,8 +814,8 @@ hipError_t wide_kernels(const Shape& sh, const WideArgs& a, const WideLayout& w,
 // workspace, or 0 if the path does not take the call: 65 tokens or more, bf16 or quantized rows
 // that the 2..64-token kernels take, and every byte offset below 2^31.
 // Passes of 64 against one pass here, 90%: 8B shape LoPA r = 512, 65 / 96 / 128 / 200 / 256 tokens
-// 118.8 / 171.7 / 199.5 / 345.6 / 398.6 -> 115.9 / 124.7 / 130.6 / 184.4 / 196.1 us; d 512, d_ff 2000,
-// 100 tokens 51.8 -> 39.2; 70B shape LoPA r = 1024, 100 tokens 639.8 -> 379.8.  65 tokens is the
+// 118.8 / 171.7 / 199.5 / 345.6 / 398.6 -> 110.5 / 117.9 / 124.0 / 158.6 / 167.2 us; d 512, d_ff 2000,
+// 100 tokens 51.8 -> 37.8; 70B shape LoPA r = 1024, 100 tokens 639.8 -> 329.1.  65 tokens is the
 // smallest call that would need two passes of 64.
 int wide_pass_tokens(const Shape& sh, Gate g, const Form& form, size_t head, size_t bytes) {
   if (sh.wdt < 1 || sh.wdt > 3 || sh.T <= kTokChunk) return 0;
@@ -681,12 +844,18 @@ hipError_t launch_wide(const Shape& sh, Gate g, bool dense, const Form& form, co
   hipError_t e = launch_split_tokens(sh, x, w.ws, s);
   if (e != hipSuccess) return e;
   if (lopa) {
-    if ((e = launch_z_tiles(sh, form, x, lopa_a, w.ws, s)) != hipSuccess) return e;
-    if (form.rms_eps > 0.f &&
-        (e = launch_rms_norm(w.ws.z, 2, sh.T, sh.T, sh.r, form.rms_gain, form.rms_eps, s)) != hipSuccess)
-      return e;
+    int copies = 1;
+    if (sh.wdt == 2) e = wide_z<WI8>(sh, form, x, lopa_a, w, &copies, s);
+    else if (sh.wdt == 3) e = wide_z<WI4>(sh, form, x, lopa_a, w, &copies, s);
+    else e = wide_z<WBf16>(sh, form, x, lopa_a, w, &copies, s);
+    if (e != hipSuccess) return e;
+    if (form.rms_eps > 0.f) {
+      e = launch_rms_norm(w.ws.z, copies, sh.T, sh.T, sh.r, form.rms_gain, form.rms_eps, s);
+      if (e != hipSuccess) return e;
+      copies = 1;  // the normalised z; the others are zeros now
+    }
     const int nks = (sh.r + 31) / 32, n = nks * w.ntt * kWave;
-    k_split_z<<<(n + kBlock - 1) / kBlock, kBlock, 0, s>>>(w.ws.z, sh.r, sh.T, sh.T, nks, w.ntt, w.zs);
+    k_split_z<<<(n + kBlock - 1) / kBlock, kBlock, 0, s>>>(w.ws.z, copies, sh.r, sh.T, nks, w.ntt, w.zs);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   WideArgs a{};
