@@ -1106,11 +1106,6 @@ __device__ __forceinline__ void dn_issue(DnFrags<NT, W>& f, const DnRows<NT, W>&
                                : kOOB));
 }
 
-template <int I>
-struct Int {
-  static constexpr int value = I;
-};
-
 // tile: this wave's LDS tile (32 PITCH uint4).  Within each 16-lane group q of the
 // transposing read, lane 4a + b addresses 8 bytes (4 columns) of one tile row and lane
 // 4b + c receives element c of the chunks of lanes b, 4 + b, 8 + b, 12 + b.  With lane
@@ -1521,6 +1516,8 @@ hipError_t launch_split_tokens(const Shape& sh, const float* x, const Workspace&
 hipError_t launch_batched(const Shape& sh, Gate g, bool dense, const Form& form, const float* x,
                           const void* lopa_a, const void* gate_w, const void* w_up, const void* w_down_t, float t,
                           Workspace& ws, float* y, hipStream_t s) {
+  if (wide64_ok(sh, g, ws))
+    return launch_wide64(sh, g, dense, form, x, lopa_a, gate_w, w_up, w_down_t, t, ws, y, s);
   hipError_t e = hipSuccess;
   // more than one token tile: the kernels read the tokens pre-split
   if (sh.T > 16 &&

@@ -166,5 +166,11 @@ int wide_pass_tokens(const Shape& sh, Gate g, const Form& form, size_t head, siz
 hipError_t launch_wide(const Shape& sh, Gate g, bool dense, const Form& form, const float* x, const void* lopa_a,
                        const void* gate_w, const void* w_up, const void* w_down_t, float t, void* base, size_t head,
                        float* y, hipStream_t s);
+// A pass of kWide64Min .. kTokChunk tokens on the same kernels, in the workspace's own regions.
+constexpr int kWide64Min = 33;
+bool wide64_ok(const Shape& sh, Gate g, const Workspace& ws);
+hipError_t launch_wide64(const Shape& sh, Gate g, bool dense, const Form& form, const float* x, const void* lopa_a,
+                         const void* gate_w, const void* w_up, const void* w_down_t, float t, Workspace& ws, float* y,
+                         hipStream_t s);
 
 }  // namespace ffn

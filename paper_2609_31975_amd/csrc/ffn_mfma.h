@@ -39,6 +39,11 @@ constexpr uint32_t tok_bytes() {  // bytes of a token's fp32 chunk
 __device__ __forceinline__ f32x4_t mfma16f(float a, float b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
+template <int I>
+struct Int {
+  static constexpr int value = I;
+};
+
 template <int J>
 __device__ __forceinline__ float comp(const uint4& v) {
   return __uint_as_float(J == 0 ? v.x : J == 1 ? v.y : J == 2 ? v.z : v.w);

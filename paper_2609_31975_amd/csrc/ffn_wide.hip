@@ -1,4 +1,5 @@
-// gfx950 kernels for calls of more than 64 tokens with bf16 or int8 / int4 weights.
+// gfx950 kernels for calls of more than 64 tokens with bf16 or int8 / int4 weights, and of 33..64
+// where d_ff suits them (wide64_ok).
 //
 // A pass of the 2..64-token kernels re-reads every token for each 64 weight rows and every
 // weight row for each 64 tokens: at 200 tokens (8B shape, LoPA r = 512) four passes took 345 us,
@@ -41,6 +42,7 @@ constexpr int kWDnSegs = 128;               // most segments of it
 constexpr int kWDnPad = 10;  // iterations past the last one that the down loop looks at
 constexpr int kWDnList = kWDnRows + 3 * kWDnSegs + 64 * (kWDnPad + 1);  // packed entries, see k_wide_down
 constexpr int kXcds = 8;
+constexpr int kWCus = 256;
 
 // Workgroup b of a grid of units x blocks: the blocks of a unit are kXcds apart, on one XCD.
 __device__ __forceinline__ void unit_of(int b, int nb, int* unit, int* blk) {
@@ -75,9 +77,10 @@ __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70)
 // the row index xor-ed with the chunk's place in the iteration so that a row's eight chunks, which
 // neighbouring lanes write, fall on distinct banks), and the tokens' hi and lo planes as they are
 // in memory.
+template <int NT>
 struct WideStage {
-  uint4 w[2][2][kWTiles][4][16];
-  uint4 x[2][2][2][kWTiles][kWave];  // [buffer][plane][k step][token tile][lane]
+  uint4 w[2][2][NT][4][16];
+  uint4 x[2][2][2][NT][kWave];  // [buffer][plane][k step][token tile][lane]
 };
 
 // acc[i][j] += rows (row tile wr + 2 i) . tokens (token tile wt + 2 j) for a wave (kg, wr, wt) over
@@ -93,10 +96,12 @@ struct WideRows {
   static constexpr int NL = (32 * RT + RPP - 1) / RPP;
 };
 
-template <class W, int RT>
-__device__ __forceinline__ void wide_product(WideStage& st, const Buf& wb, int C, const int* roff, const Buf& xb,
+template <class W, int RT, int NT>
+__device__ __forceinline__ void wide_product(WideStage<NT>& st, const Buf& wb, int C, const int* roff, const Buf& xb,
                                              uint32_t part_bytes, int ntt, int nt0, int ntb, int it0, int it1,
-                                             f32x4_t (&acc)[RT][4]) {
+                                             f32x4_t (&acc)[RT][NT / 2]) {
+  constexpr int NJ = NT / 2;  // token tiles of a wave
+  static_assert(2 * RT <= NT, "the row tiles' space");
   using S = WideRows<W, RT>;
   const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid / kWave);
   const int nks = (C + 3) / 4, nit = it1 - it0;
@@ -104,10 +109,14 @@ __device__ __forceinline__ void wide_product(WideStage& st, const Buf& wb, int C
   struct RegsW {
     uint4 w[S::NL];
   };
+  // a wave loads token tile wave % NT: with eight tiles both k steps of an iteration, with four
+  // k step wave / 4
+  constexpr int NK = NT / 4;
   struct RegsX {
-    uint4 x[2][2];  // [plane][k step]
+    uint4 x[2][NK];  // [plane][k step]
   };
-  const bool tile_ok = wave < ntb;
+  const int lt = wave % NT, lk = wave / NT;
+  const bool tile_ok = lt < ntb;
   auto load_w = [&](RegsW& r, int t) {
     const int it = it0 + t, lc = tid % S::LPR, ch = it * S::LPR + lc;  // the lane's loaded chunk of the row
     const bool cv = it < it1 && ch < C / S::R8;
@@ -117,10 +126,10 @@ __device__ __forceinline__ void wide_product(WideStage& st, const Buf& wb, int C
   auto load_x = [&](RegsX& r, int t) {
     const int it = it0 + t;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int ks = 2 * it + k;
+    for (int k = 0; k < NK; ++k) {
+      const int ks = 2 * it + lk + k;
       const uint32_t off = tile_ok && it < it1 && ks < nks
-                               ? 16u * ((uint32_t)(ks * ntt + nt0 + wave) * kWave + (uint32_t)lane)
+                               ? 16u * ((uint32_t)(ks * ntt + nt0 + lt) * kWave + (uint32_t)lane)
                                : kOOB;
       r.x[0][k] = ldb(xb, off);
       r.x[1][k] = ldb(xb, off + part_bytes);
@@ -144,7 +153,7 @@ __device__ __forceinline__ void wide_product(WideStage& st, const Buf& wb, int C
   };
   auto put_x = [&](const RegsX& r, int b, int p) {
 #pragma unroll
-    for (int k = 0; k < 2; ++k) st.x[b][p][k][wave][lane] = r.x[p][k];
+    for (int k = 0; k < NK; ++k) st.x[b][p][lk + k][lt][lane] = r.x[p][k];
   };
   // operands of the wave's k step of the tile in buffer b
   auto read_a = [&](int b, int i) { return bf8(st.w[b][kg][wr + 2 * i][g][m ^ (2 * g + 8 * kg)]); };
@@ -158,7 +167,7 @@ __device__ __forceinline__ void wide_product(WideStage& st, const Buf& wb, int C
   // and add zeros), so that no load sits on a conditional path.
   RegsW w0, w1, w2, w3;
   RegsX x0, x1;
-  bf16x8_t a0[RT], a1[RT], xh[4], xl[4];
+  bf16x8_t a0[RT], a1[RT], xh[NJ], xl[NJ];
   load_w(w0, 0), load_x(x0, 0);
   load_w(w1, 1), load_x(x1, 1);
   load_w(w2, 2), load_w(w3, 3);
@@ -170,15 +179,16 @@ __device__ __forceinline__ void wide_product(WideStage& st, const Buf& wb, int C
 #pragma unroll
   for (int i = 0; i < RT; ++i) a0[i] = read_a(0, i);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < NJ; ++j) {
     xh[j] = read_x(0, 0, j);
     xl[j] = read_x(0, 1, j);
   }
   __syncthreads();
   auto step = [&](const bf16x8_t (&a)[RT], bf16x8_t (&an)[RT], RegsW& w, RegsX& x, int b, int t) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (j < RT) an[j] = read_a(b ^ 1, j);
+    for (int j = 0; j < NJ; ++j) {
+#pragma unroll
+      for (int i = j; i < RT; i += NJ) an[i] = read_a(b ^ 1, i);
 #pragma unroll
       for (int i = 0; i < RT; ++i) acc[i][j] = mfma16(a[i], xh[j], acc[i][j]);
 #pragma unroll
@@ -190,7 +200,7 @@ __device__ __forceinline__ void wide_product(WideStage& st, const Buf& wb, int C
         load_w(w, t + 6);
       }
       if (j == 1) put_x(x, b, 0);
-      if (j == 2) {
+      if (j == NJ / 2) {
         put_x(x, b, 1);
         load_x(x, t + 4);
       }
@@ -221,6 +231,9 @@ struct WideArgs {
   int32_t* seg_idx;                   // [nb][d_ff]
   uint4* zf;   // zval by quads: block b's quads at uint4 16 nt0(b) nseg qps, of segment seg from quad
                // seg qps, [quad][token tile of the block][16]
+  float* seg_act;  // calls of at most kTokChunk tokens: [T][d_ff], act of entry e of segment w at slot
+                   // start(w) + e (the inspection hooks' layout), else null
+  int32_t* meta;   // likewise: meta[0] = nseg
   float* y;
 };
 __host__ __device__ __forceinline__ int wide_iterations(int C) { return (C + 7) / 8; }
@@ -231,12 +244,14 @@ __device__ __forceinline__ uint32_t plane_bytes(int C, int ntt) {
 // Gate, union and W_up of one segment (up to 32 RT rows) for one block of tokens.  The activation
 // values wait in the segment's own part of the zval buffer ([row][token of the block], the same
 // size) for the W_up sums: they are read back before the first zval is written there.
-template <class W>
+// NT: token tiles of a block, at most (and row tiles of a segment).
+template <class W, int NT>
 __global__ __launch_bounds__(kWThreads) void k_wide_gate_up(WideArgs a) {
   constexpr bool Q = is_quant<W>();
+  constexpr int NJ = NT / 2;
   __shared__ union {
-    WideStage st;
-    f32x4_t join[8 * 2 * 4 * kWave];
+    WideStage<NT> st;
+    f32x4_t join[8 * (NT / 4) * NJ * kWave];
   } s;
   __shared__ uint32_t s_mask[kWTiles];
   __shared__ int s_list[kWRows];
@@ -252,6 +267,7 @@ __global__ __launch_bounds__(kWThreads) void k_wide_gate_up(WideArgs a) {
   const int row0 = segs.start(seg), nrows = segs.start(seg + 1) - row0;  // <= kWRows
   uint4* const zq = a.zf + ((size_t)nt0 * a.nseg + (size_t)seg * ntb) * a.qps * 16;
   float* const act = reinterpret_cast<float*>(zq);  // [nrows][16 ntb]
+  if (a.meta && blockIdx.x == 0 && tid == 0) a.meta[0] = a.nseg;
   if (tid < kWTiles) s_mask[tid] = 0u;
 
   // the rows of a product: rows list[k], k < n, of a matrix of C chunks a row
@@ -269,8 +285,8 @@ __global__ __launch_bounds__(kWThreads) void k_wide_gate_up(WideArgs a) {
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    wide_product<W, RT>(s.st, make_buf(mat, 16u * (uint32_t)a.d_ff * (uint32_t)Cl), C, roff, make_buf(planes, 2 * part),
+      for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    wide_product<W, RT, NT>(s.st, make_buf(mat, 16u * (uint32_t)a.d_ff * (uint32_t)Cl), C, roff, make_buf(planes, 2 * part),
                         part, a.ntt, nt0, ntb, 0, wide_iterations(C), acc);
   };
 
@@ -279,7 +295,7 @@ __global__ __launch_bounds__(kWThreads) void k_wide_gate_up(WideArgs a) {
   auto gate = [&](auto& acc) {
     constexpr int RT = sizeof(acc) / sizeof(acc[0]);
     product(a.gate_w, a.Cg, a.lopa ? a.zs : a.xs, nrows, [&](int k) { return row0 + k; }, acc);
-    f32x4_t h[RT / 2][4];
+    f32x4_t h[RT / 2][NJ];
     join_k(acc, s.join, h);
     const Buf qb = make_buf(a.s_g, 4u * (uint32_t)a.d_ff);
     const bool has_g = a.lopa && a.form.g_idx;
@@ -294,7 +310,7 @@ __global__ __launch_bounds__(kWThreads) void k_wide_gate_up(WideArgs a) {
         const float sc = Q ? __int_as_float(ldb32(qb, rv ? 4u * (uint32_t)(row0 + rl) : kOOB)) : 1.f;
         bool any = false;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < NJ; ++j) {
           const int nt = wt + 2 * j, tok = 16 * (nt0 + nt) + m;
           const bool tv = nt < ntb && tok < a.T;
           float hv = h[i][j][e];
@@ -313,11 +329,16 @@ __global__ __launch_bounds__(kWThreads) void k_wide_gate_up(WideArgs a) {
     }
   };
   __syncthreads();
-  if (nrows <= kWRows / 2) {
-    f32x4_t acc[2][4];
-    gate(acc);
+  if constexpr (NT == kWTiles) {
+    if (nrows > kWRows / 2) {
+      f32x4_t acc[4][NJ];
+      gate(acc);
+    } else {
+      f32x4_t acc[2][NJ];
+      gate(acc);
+    }
   } else {
-    f32x4_t acc[4][4];
+    f32x4_t acc[2][NJ];
     gate(acc);
   }
   wait_vmem();  // the activation values are out
@@ -346,13 +367,18 @@ __global__ __launch_bounds__(kWThreads) void k_wide_gate_up(WideArgs a) {
     if (tid == 0) a.seg_count[blk * a.nseg + seg] = cnt;
   }
   __syncthreads();
+  if (a.seg_act)
+    for (int o = tid; o < cnt * 16 * ntb; o += kWThreads) {  // lanes along the entries
+      const int tok = o / cnt, e = o - tok * cnt;
+      if (tok < a.T) a.seg_act[(size_t)tok * a.d_ff + row0 + e] = act[(size_t)s_list[e] * 16 * ntb + tok];
+    }
   if (cnt == 0) return;  // workgroup-uniform
 
   // W_up dots of the union rows, then zval = activation value times the dot
   auto up = [&](auto& acc) {
     constexpr int RT = sizeof(acc) / sizeof(acc[0]);
     product(a.w_up, a.Cu, a.xs, cnt, [&](int k) { return row0 + s_list[k]; }, acc);
-    float av[RT / 2][4][4], su[RT / 2][4], sd[RT / 2][4];
+    float av[RT / 2][NJ][4], su[RT / 2][4], sd[RT / 2][4];
     const Buf ubs = make_buf(a.s_up, 4u * (uint32_t)a.d_ff), dbs = make_buf(a.s_down, 4u * (uint32_t)a.d_ff);
 #pragma unroll
     for (int i = 0; i < RT / 2; ++i)
@@ -366,12 +392,12 @@ __global__ __launch_bounds__(kWThreads) void k_wide_gate_up(WideArgs a) {
           sd[i][e] = __int_as_float(ldb32(dbs, off));
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < NJ; ++j) {
           const int nt = wt + 2 * j;
           av[i][j][e] = en < cnt && nt < ntb ? act[(size_t)rl * 16 * ntb + 16 * nt + m] : 0.f;
         }
       }
-    f32x4_t v[RT / 2][4];
+    f32x4_t v[RT / 2][NJ];
     join_k(acc, s.join, v);
     wait_vmem();
     __syncthreads();  // every activation value has been read
@@ -380,7 +406,7 @@ __global__ __launch_bounds__(kWThreads) void k_wide_gate_up(WideArgs a) {
       const int q = 4 * (wr + 2 * (kg * (RT / 2) + i)) + g;
       if (4 * q >= cnt) continue;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < NJ; ++j) {
         const int nt = wt + 2 * j;
         if (nt >= ntb) continue;
         uint32_t hw[2] = {0u, 0u}, lw[2] = {0u, 0u};
@@ -398,11 +424,16 @@ __global__ __launch_bounds__(kWThreads) void k_wide_gate_up(WideArgs a) {
       }
     }
   };
-  if (cnt <= kWRows / 2) {
-    f32x4_t acc[2][4];
-    up(acc);
+  if constexpr (NT == kWTiles) {
+    if (cnt > kWRows / 2) {
+      f32x4_t acc[4][NJ];
+      up(acc);
+    } else {
+      f32x4_t acc[2][NJ];
+      up(acc);
+    }
   } else {
-    f32x4_t acc[4][4];
+    f32x4_t acc[2][NJ];
     up(acc);
   }
 }
@@ -412,20 +443,20 @@ __global__ __launch_bounds__(kWThreads) void k_wide_gate_up(WideArgs a) {
 // them for each k group.  The rows go to LDS as they are (two pad chunks a row: the transposing
 // reads' eight rows on distinct banks), the zval quads beside them.  The k groups' sums meet in LDS,
 // then go to y with one fp32 atomic per token and column.
-template <class W>
+template <class W, int NT>
 __global__ __launch_bounds__(kWThreads) void k_wide_down(const int32_t* __restrict__ seg_count,
                                                          const int32_t* __restrict__ seg_idx,
                                                          const uint4* __restrict__ zf, int nseg, int qps, int d_ff,
                                                          int R, int ntt, int nb, const uint4* __restrict__ w_down_t,
                                                          int C, int d, int T, float* __restrict__ y) {
   constexpr int R8 = W::EPC / 8, LPR = kWCols / W::EPC, RPP = kWThreads / LPR, NL = (64 + RPP - 1) / RPP;
-  constexpr int PITCH = kWCols / 8 + 2;
+  constexpr int PITCH = kWCols / 8 + 2, NJ = NT / 2;
   __shared__ union {
     struct {
       uint4 w[2][64 * PITCH];
-      uint4 z[2][2][2][kWTiles][kWave];  // [buffer][k group][hi, lo][token tile][lane]
+      uint4 z[2][2][2][NT][kWave];  // [buffer][k group][hi, lo][token tile][lane]
     } st;
-    f32x4_t join[8 * 2 * 4 * kWave];
+    f32x4_t join[8 * (NJ / 2) * 4 * kWave];
   } s;
   __shared__ int s_row[kWDnList], s_zq[kWDnList / 4];
   __shared__ int s_wquads[kWThreads / kWave], s_cnt[kWDnSegs], s_quad[kWDnSegs];
@@ -492,23 +523,27 @@ __global__ __launch_bounds__(kWThreads) void k_wide_down(const int32_t* __restri
   }
   __syncthreads();
 
-  f32x4_t acc[4][4];  // [token tile wt + 2 j][16 columns 64 wc + 16 c]
+  f32x4_t acc[NJ][4];  // [token tile wt + 2 j][16 columns 64 wc + 16 c]
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+  for (int j = 0; j < NJ; ++j)
 #pragma unroll
     for (int cc = 0; cc < 4; ++cc) acc[j][cc] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   struct RegsW {
     uint4 w[NL];
   };
+  // a wave loads the zval of token tile wave % NT: with eight tiles both k groups of an iteration,
+  // with four k group wave / 4
+  constexpr int NK = NT / 4;
+  const int lt = wave % NT, lk = wave / NT;
   struct RegsZ {
-    u32x4_t z[4];
+    u32x4_t z[2 * NK];
   };
   struct Place {  // list entries of a load
-    int row[NL], zq[4];
+    int row[NL], zq[2 * NK];
   };
   const int lc = tid % LPR, ch = cgrp * LPR + lc;
-  const bool tile_ok = wave < ntb;
+  const bool tile_ok = lt < ntb;
   auto rows = [&](Place& a, int it) {
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
@@ -518,7 +553,7 @@ __global__ __launch_bounds__(kWThreads) void k_wide_down(const int32_t* __restri
   };
   auto zqs = [&](Place& a, int it) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) a.zq[j] = s_zq[16 * it + 4 * j + g];
+    for (int j = 0; j < 2 * NK; ++j) a.zq[j] = s_zq[16 * it + 8 * lk + 4 * j + g];
   };
   auto load_w = [&](RegsW& r, const Place& a) {
 #pragma unroll
@@ -527,10 +562,10 @@ __global__ __launch_bounds__(kWThreads) void k_wide_down(const int32_t* __restri
   };
   auto load_z = [&](RegsZ& r, const Place& a) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 2 * NK; ++j)
       r.z[j] = __builtin_bit_cast(
           u32x4_t, ldb(zb, tile_ok && a.zq[j] >= 0
-                               ? 16u * (((uint32_t)a.zq[j] * (uint32_t)ntb + (uint32_t)wave) * 16u + (uint32_t)m)
+                               ? 16u * (((uint32_t)a.zq[j] * (uint32_t)ntb + (uint32_t)lt) * 16u + (uint32_t)m)
                                : kOOB));
   };
   auto put_w = [&](const RegsW& r, int b) {
@@ -540,12 +575,15 @@ __global__ __launch_bounds__(kWThreads) void k_wide_down(const int32_t* __restri
       if (e < 64) put_bf16_chunks<W>(&s.st.w[b][e * PITCH + lc * R8], r.w[i]);
     }
   };
-  // the quads 4 g and 16 + 4 g of k group k's 32 entries as one hi and one lo operand
-  auto put_z = [&](const RegsZ& r, int b, int k) {
-    s.st.z[b][k][0][wave][lane] =
-        __builtin_bit_cast(uint4, __builtin_shufflevector(r.z[2 * k], r.z[2 * k + 1], 0, 1, 4, 5));
-    s.st.z[b][k][1][wave][lane] =
-        __builtin_bit_cast(uint4, __builtin_shufflevector(r.z[2 * k], r.z[2 * k + 1], 2, 3, 6, 7));
+  // the quads 4 g and 16 + 4 g of the 32 entries of k group lk + k as one hi and one lo operand
+  auto put_z = [&](const RegsZ& r, int b, auto kc) {
+    constexpr int k = decltype(kc)::value;
+    if constexpr (k < NK) {
+      s.st.z[b][lk + k][0][lt][lane] =
+          __builtin_bit_cast(uint4, __builtin_shufflevector(r.z[2 * k], r.z[2 * k + 1], 0, 1, 4, 5));
+      s.st.z[b][lk + k][1][lt][lane] =
+          __builtin_bit_cast(uint4, __builtin_shufflevector(r.z[2 * k], r.z[2 * k + 1], 2, 3, 6, 7));
+    }
   };
   // The transposing reads as in k_down_mfma: 32 entries of the k group, 16 of the wave's 64 columns.
   auto read_d = [&](int b, int cc) {
@@ -559,7 +597,7 @@ __global__ __launch_bounds__(kWThreads) void k_wide_down(const int32_t* __restri
   if (nit > 0) {  // the loop of wide_product, the list entries read one iteration ahead of their loads
     RegsW w0, w1, w2, w3;
     RegsZ z0, z1;
-    bf16x8_t d0[4], d1[4], zh[4], zl[4];
+    bf16x8_t d0[4], d1[4], zh[NJ], zl[NJ];
     Place a;
     rows(a, 0), zqs(a, 0);
     load_w(w0, a), load_z(z0, a);
@@ -570,24 +608,26 @@ __global__ __launch_bounds__(kWThreads) void k_wide_down(const int32_t* __restri
     rows(a, 3);
     load_w(w3, a);
     rows(a, 4), zqs(a, 2);
-    put_w(w0, 0), put_z(z0, 0, 0), put_z(z0, 0, 1);
+    put_w(w0, 0), put_z(z0, 0, Int<0>{}), put_z(z0, 0, Int<1>{});
     load_w(w0, a), load_z(z0, a);
     rows(a, 5), zqs(a, 3);
-    put_w(w1, 1), put_z(z1, 1, 0), put_z(z1, 1, 1);
+    put_w(w1, 1), put_z(z1, 1, Int<0>{}), put_z(z1, 1, Int<1>{});
     load_w(w1, a), load_z(z1, a);
     rows(a, 6), zqs(a, 4);
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      d0[j] = read_d(0, j);
+    for (int cc = 0; cc < 4; ++cc) d0[cc] = read_d(0, cc);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
       zh[j] = read_z(0, 0, j);
       zl[j] = read_z(0, 1, j);
     }
     __syncthreads();
     auto step = [&](const bf16x8_t (&dc)[4], bf16x8_t (&dn)[4], RegsW& w, RegsZ& z, int b, int t) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        dn[j] = read_d(b ^ 1, j);
+      for (int j = 0; j < NJ; ++j) {
+#pragma unroll
+        for (int cc = j; cc < 4; cc += NJ) dn[cc] = read_d(b ^ 1, cc);
 #pragma unroll
         for (int cc = 0; cc < 4; ++cc) acc[j][cc] = mfma16(zh[j], dc[cc], acc[j][cc]);
 #pragma unroll
@@ -598,12 +638,12 @@ __global__ __launch_bounds__(kWThreads) void k_wide_down(const int32_t* __restri
           put_w(w, b);
           load_w(w, a);
         }
-        if (j == 1) put_z(z, b, 0);
-        if (j == 2) {
-          put_z(z, b, 1);
+        if (j == 1) put_z(z, b, Int<0>{});
+        if (j == NJ / 2) {
+          put_z(z, b, Int<1>{});
           load_z(z, a);
         }
-        if (j == 3) {
+        if (j == NJ - 1) {
           rows(a, t + 7);
           zqs(a, t + 5);
         }
@@ -619,11 +659,11 @@ __global__ __launch_bounds__(kWThreads) void k_wide_down(const int32_t* __restri
       if (t + 4 >= nit) break;
     }
   }
-  f32x4_t f[2][4];
+  f32x4_t f[NJ / 2][4];
   join_k(acc, s.join, f);
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int nt = wt + 2 * (2 * kg + j);
+  for (int j = 0; j < NJ / 2; ++j) {
+    const int nt = wt + 2 * (NJ / 2 * kg + j);
     if (nt >= ntb) continue;
 #pragma unroll
     for (int cc = 0; cc < 4; ++cc) {
@@ -642,14 +682,15 @@ __global__ __launch_bounds__(kWThreads) void k_wide_down(const int32_t* __restri
 // zp[p][T][r].  The parts spread the few rows of A over the chip (r = 512, 200 tokens: 16 units, 16
 // parts of four iterations each: 9.4 us; 19.6 on the batch kernels' grid of 16-row
 // tiles, each with workgroups for every token tile); k_split_z adds them.
-template <class W>
+template <class W, int NT>
 __global__ __launch_bounds__(kWThreads) void k_wide_z(const uint4* __restrict__ A, const uint4* __restrict__ xs, int C,
                                                       int T, int r, int ntt, int nb, int P, float* __restrict__ zp,
                                                       const float* __restrict__ s_a, GWork gw) {
   if (g_precompute(gw)) return;
+  constexpr int NJ = NT / 2;
   __shared__ union {
-    WideStage st;
-    f32x4_t join[8 * 2 * 4 * kWave];
+    WideStage<NT> st;
+    f32x4_t join[8 * NJ * kWave];
   } s;
   const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid / kWave);
   const int kg = wave >> 2, wr = (wave >> 1) & 1, wt = wave & 1, m = lane & 15, g = lane >> 4;
@@ -667,21 +708,21 @@ __global__ __launch_bounds__(kWThreads) void k_wide_z(const uint4* __restrict__ 
     const int k = tid / S::LPR + S::RPP * i;
     roff[i] = k < n ? (row0 + k) * Cl : -1;
   }
-  f32x4_t acc[RT][4];
+  f32x4_t acc[RT][NJ];
 #pragma unroll
   for (int i = 0; i < RT; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  wide_product<W, RT>(s.st, make_buf(A, 16u * (uint32_t)r * (uint32_t)Cl), C, roff, make_buf(xs, 2 * part), part, ntt,
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  wide_product<W, RT, NT>(s.st, make_buf(A, 16u * (uint32_t)r * (uint32_t)Cl), C, roff, make_buf(xs, 2 * part), part, ntt,
                       nt0, ntb, its.start(p), its.start(p + 1), acc);
-  f32x4_t f[RT / 2][4];
+  f32x4_t f[RT / 2][NJ];
   join_k(acc, s.join, f);
 #pragma unroll
   for (int i = 0; i < RT / 2; ++i) {
     const int kl = 16 * (wr + 2 * (kg * (RT / 2) + i)) + 4 * g, k = row0 + kl;
     if (kl >= n) continue;  // r is a multiple of 8: four rows or none
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < NJ; ++j) {
       const int tok = 16 * (nt0 + wt + 2 * j) + m;
       f32x4_t v = f[i][j];
       if constexpr (is_quant<W>()) {
@@ -725,8 +766,9 @@ struct WideLayout {
   int nseg, qps, ntt, nb;
   int zparts;    // partial copies of z there is room for
   Workspace ws;  // tc, z, gx, xs of the shared kernels
-  int32_t *seg_count, *seg_idx;
+  int32_t *seg_count, *seg_idx, *meta;
   uint4 *zs, *zf;
+  float* seg_act;
 };
 
 // The pass's regions in the workspace, behind the z slots (which stay as they are); returns the bytes.
@@ -767,11 +809,11 @@ size_t wide_layout(int T, int d, int d_ff, int r, bool has_g, void* base, size_t
 }
 
 // z's partial copies, `*parts` of them: about one workgroup a CU, at least four iterations each.
-template <class W>
+template <class W, int NT>
 hipError_t wide_z(const Shape& sh, const Form& form, const float* x, const void* lopa_a, const WideLayout& w, int* parts,
                   hipStream_t s) {
   const int C = sh.d / 8, units = (sh.r + kZRows - 1) / kZRows * w.nb;
-  int P = (256 + units - 1) / units;
+  int P = (kWCus + units - 1) / units;
   const int most = wide_iterations(C) / 4;
   if (P > most) P = most;
   if (P > w.zparts) P = w.zparts;
@@ -780,20 +822,20 @@ hipError_t wide_z(const Shape& sh, const Form& form, const float* x, const void*
   const int grid = units * P;
   const GWork gw{form, x, w.ws.gx, sh.T, sh.d, sh.d_ff, grid};
   const int extra = form.g_idx ? (g_items(sh.d_ff, sh.T) + kWThreads - 1) / kWThreads : 0;
-  k_wide_z<W><<<grid + extra, kWThreads, 0, s>>>(static_cast<const uint4*>(lopa_a), w.ws.xs, C, sh.T, sh.r, w.ntt, w.nb, P,
+  k_wide_z<W, NT><<<grid + extra, kWThreads, 0, s>>>(static_cast<const uint4*>(lopa_a), w.ws.xs, C, sh.T, sh.r, w.ntt, w.nb, P,
                                                  w.ws.z, sh.sc.a, gw);
   return hipGetLastError();
 }
 
-template <class W>
+template <class W, int NT>
 hipError_t wide_kernels(const Shape& sh, const WideArgs& a, const WideLayout& w, const void* w_down_t, hipStream_t s) {
   const int units = (w.nseg + kXcds - 1) / kXcds * kXcds;
-  const hipError_t e = launch_gate_kernel_n(k_wide_gate_up<W>, units * w.nb, kWThreads, s, a);
+  const hipError_t e = launch_gate_kernel_n(k_wide_gate_up<W, NT>, units * w.nb, kWThreads, s, a);
   if (e != hipSuccess) return e;
   // Down grid: about one workgroup a CU, chunks of at least 512 rows (each chunk adds T d fp32
   // atomics) and at most kWDnRows, kWDnSegs.
   const int S = (sh.d + kWCols - 1) / kWCols;
-  int R = (256 + S * w.nb - 1) / (S * w.nb);
+  int R = (kWCus + S * w.nb - 1) / (S * w.nb);
   const int most = (sh.d_ff + 511) / 512;
   if (R > most) R = most;
   const int rows = (sh.d_ff + w.nseg - 1) / w.nseg;
@@ -803,51 +845,23 @@ hipError_t wide_kernels(const Shape& sh, const WideArgs& a, const WideLayout& w,
   if (R < least) R = least;
   if (R > w.nseg) R = w.nseg;
   const int du = (S * R + kXcds - 1) / kXcds * kXcds;
-  k_wide_down<W><<<du * w.nb, kWThreads, 0, s>>>(w.seg_count, w.seg_idx, w.zf, w.nseg, w.qps, sh.d_ff, R, w.ntt, w.nb,
+  k_wide_down<W, NT><<<du * w.nb, kWThreads, 0, s>>>(w.seg_count, w.seg_idx, w.zf, w.nseg, w.qps, sh.d_ff, R, w.ntt, w.nb,
                                                  static_cast<const uint4*>(w_down_t), sh.d / W::EPC, sh.d, sh.T, a.y);
   return hipGetLastError();
 }
 
-}  // namespace
-
-// Tokens of a pass: the most (a multiple of 16, at most kWidePass) whose regions fit `bytes` of
-// workspace, or 0 if the path does not take the call: 65 tokens or more, bf16 or quantized rows
-// that the 2..64-token kernels take, and every byte offset below 2^31.
-// Passes of 64 against one pass here, 90%: 8B shape LoPA r = 512, 65 / 96 / 128 / 200 / 256 tokens
-// 118.8 / 171.7 / 199.5 / 345.6 / 398.6 -> 110.5 / 117.9 / 124.0 / 158.6 / 167.2 us; d 512, d_ff 2000,
-// 100 tokens 51.8 -> 37.8; 70B shape LoPA r = 1024, 100 tokens 639.8 -> 329.1.  65 tokens is the
-// smallest call that would need two passes of 64.
-int wide_pass_tokens(const Shape& sh, Gate g, const Form& form, size_t head, size_t bytes) {
-  if (sh.wdt < 1 || sh.wdt > 3 || sh.T <= kTokChunk) return 0;
-  Shape one = sh;
-  one.T = kTokChunk;
-  if (!batched_ok(one, g)) return 0;
-  const int64_t lim = int64_t(1) << 31;
-  const int r = g == Gate::LoPA ? sh.r : 0;
-  for (int t = kWidePass; t > kTokChunk; t -= 16) {
-    WideLayout w;
-    if (wide_layout(t, sh.d, sh.d_ff, r, form.g_idx != nullptr, nullptr, head, &w) > bytes) continue;
-    if (256 * (int64_t)w.nseg * w.qps * kWTiles >= lim || 4 * (int64_t)t * sh.d >= lim / 4 ||
-        4 * (int64_t)t * (r > 0 ? r : 1) >= lim / 4)
-      continue;
-    return t;
-  }
-  return 0;
-}
-
-hipError_t launch_wide(const Shape& sh, Gate g, bool dense, const Form& form, const float* x, const void* lopa_a,
-                       const void* gate_w, const void* w_up, const void* w_down_t, float t, void* base, size_t head,
-                       float* y, hipStream_t s) {
+template <int NT>
+hipError_t wide_format(const Shape& sh, Gate g, bool dense, const Form& form, const float* x, const void* lopa_a,
+                       const void* gate_w, const void* w_up, const void* w_down_t, float t, const WideLayout& w, float* y,
+                       hipStream_t s) {
   const bool lopa = g == Gate::LoPA;
-  WideLayout w;
-  wide_layout(sh.T, sh.d, sh.d_ff, lopa ? sh.r : 0, form.g_idx != nullptr, base, head, &w);
   hipError_t e = launch_split_tokens(sh, x, w.ws, s);
   if (e != hipSuccess) return e;
   if (lopa) {
     int copies = 1;
-    if (sh.wdt == 2) e = wide_z<WI8>(sh, form, x, lopa_a, w, &copies, s);
-    else if (sh.wdt == 3) e = wide_z<WI4>(sh, form, x, lopa_a, w, &copies, s);
-    else e = wide_z<WBf16>(sh, form, x, lopa_a, w, &copies, s);
+    if (sh.wdt == 2) e = wide_z<WI8, NT>(sh, form, x, lopa_a, w, &copies, s);
+    else if (sh.wdt == 3) e = wide_z<WI4, NT>(sh, form, x, lopa_a, w, &copies, s);
+    else e = wide_z<WBf16, NT>(sh, form, x, lopa_a, w, &copies, s);
     if (e != hipSuccess) return e;
     if (form.rms_eps > 0.f) {
       e = launch_rms_norm(w.ws.z, copies, sh.T, sh.T, sh.r, form.rms_gain, form.rms_eps, s);
@@ -883,10 +897,96 @@ hipError_t launch_wide(const Shape& sh, Gate g, bool dense, const Form& form, co
   a.seg_count = w.seg_count;
   a.seg_idx = w.seg_idx;
   a.zf = w.zf;
+  a.seg_act = w.seg_act;
+  a.meta = w.meta;
   a.y = y;
-  if (sh.wdt == 2) return wide_kernels<WI8>(sh, a, w, w_down_t, s);
-  if (sh.wdt == 3) return wide_kernels<WI4>(sh, a, w, w_down_t, s);
-  return wide_kernels<WBf16>(sh, a, w, w_down_t, s);
+  if (sh.wdt == 2) return wide_kernels<WI8, NT>(sh, a, w, w_down_t, s);
+  if (sh.wdt == 3) return wide_kernels<WI4, NT>(sh, a, w, w_down_t, s);
+  return wide_kernels<WBf16, NT>(sh, a, w, w_down_t, s);
+}
+
+}  // namespace
+
+// Tokens of a pass: the most (a multiple of 16, at most kWidePass) whose regions fit `bytes` of
+// workspace, or 0 if the path does not take the call: 65 tokens or more, bf16 or quantized rows
+// that the 2..64-token kernels take, and every byte offset below 2^31.
+// Passes of 64 against one pass here, 90%: 8B shape LoPA r = 512, 65 / 96 / 128 / 200 / 256 tokens
+// 118.8 / 171.7 / 199.5 / 345.6 / 398.6 -> 110.5 / 117.9 / 124.0 / 158.6 / 167.2 us; d 512, d_ff 2000,
+// 100 tokens 51.8 -> 37.8; 70B shape LoPA r = 1024, 100 tokens 639.8 -> 329.1.  65 tokens is the
+// smallest call that would need two passes of 64.
+int wide_pass_tokens(const Shape& sh, Gate g, const Form& form, size_t head, size_t bytes) {
+  if (sh.wdt < 1 || sh.wdt > 3 || sh.T <= kTokChunk) return 0;
+  Shape one = sh;
+  one.T = kTokChunk;
+  if (!batched_ok(one, g)) return 0;
+  const int64_t lim = int64_t(1) << 31;
+  const int r = g == Gate::LoPA ? sh.r : 0;
+  for (int t = kWidePass; t > kTokChunk; t -= 16) {
+    WideLayout w;
+    if (wide_layout(t, sh.d, sh.d_ff, r, form.g_idx != nullptr, nullptr, head, &w) > bytes) continue;
+    if (256 * (int64_t)w.nseg * w.qps * kWTiles >= lim || 4 * (int64_t)t * sh.d >= lim / 4 ||
+        4 * (int64_t)t * (r > 0 ? r : 1) >= lim / 4)
+      continue;
+    return t;
+  }
+  return 0;
+}
+
+hipError_t launch_wide(const Shape& sh, Gate g, bool dense, const Form& form, const float* x, const void* lopa_a,
+                       const void* gate_w, const void* w_up, const void* w_down_t, float t, void* base, size_t head,
+                       float* y, hipStream_t s) {
+  WideLayout w;
+  wide_layout(sh.T, sh.d, sh.d_ff, g == Gate::LoPA ? sh.r : 0, form.g_idx != nullptr, base, head, &w);
+  return wide_format<kWTiles>(sh, g, dense, form, x, lopa_a, gate_w, w_up, w_down_t, t, w, y, s);
+}
+
+// The regions of a pass of at most kTokChunk tokens, all in the workspace's own: zval and z's partial
+// copies in zf (16 quads a segment of 64 rows, as there), z's planes in seg_zval.
+void wide64_layout(const Shape& sh, Gate g, const Workspace& ws, WideLayout* out) {
+  WideLayout w{};
+  w.ntt = (ws.tc + 15) / 16;
+  w.nb = 1;
+  w.nseg = (sh.d_ff + kWRows / 2 - 1) / (kWRows / 2);
+  w.qps = kWRows / 8;
+  w.ws = ws;
+  w.seg_count = ws.seg_count;
+  w.seg_idx = ws.seg_idx;
+  w.zf = ws.zf;
+  if (g == Gate::LoPA) {
+    w.zs = reinterpret_cast<uint4*>(ws.seg_zval);
+    w.ws.z = reinterpret_cast<float*>(ws.zf);
+    w.zparts = (int)(256 * (size_t)w.ntt * w.nseg * w.qps / (sizeof(float) * (size_t)sh.T * sh.r));
+  }
+  w.seg_act = ws.seg_act;
+  w.meta = ws.meta;
+  *out = w;
+}
+
+// Where 33..64 tokens take these kernels instead of the register-tiled ones: where segments of 64
+// rows leave at most an eighth or so of the compute units idle (k_gate_up_mfma balances its segments
+// over them whatever d_ff is).  LoPA r = 512 / 1024, 90%, on d_ff 14336 (224 segments): bf16 33 / 48 /
+// 64 tokens 90.9 / 105.5 / 98.7 -> 87.2 / 89.0 / 95.0 us, int8 64 tokens 97.1 -> 82.5; d_ff 28672
+// (448), 40 tokens 301 -> 256.  On d_ff 11000 (172 segments), 64 tokens 74.9 -> 88.5; 13824 (216), 33
+// tokens 112.3 -> 118.5; 2000, 64 tokens 29.9 -> 33.5; at 17 - 32 tokens, 14336: 63.4 -> 77.0 (17).
+// LoPA's z has to fit the regions above (ranks about as large as d_ff do not).
+bool wide64_ok(const Shape& sh, Gate g, const Workspace& ws) {
+  if (sh.wdt < 1 || sh.wdt > 3 || sh.T < kWide64Min || ws.tc > kTokChunk || !batched_ok(sh, g)) return false;
+  const int nseg = (sh.d_ff + kWRows / 2 - 1) / (kWRows / 2), rounds = (nseg + kWCus - 1) / kWCus;
+  if (8 * nseg < 7 * kWCus * rounds) return false;
+  if (g != Gate::LoPA) return true;
+  WideLayout w;
+  wide64_layout(sh, g, ws, &w);
+  return w.zparts >= 1 &&
+         sizeof(uint4) * 2 * (size_t)((sh.r + 31) / 32) * w.ntt * kWave <= sizeof(float) * (size_t)ws.tc * ws.slots;
+}
+
+hipError_t launch_wide64(const Shape& sh, Gate g, bool dense, const Form& form, const float* x, const void* lopa_a,
+                         const void* gate_w, const void* w_up, const void* w_down_t, float t, Workspace& ws, float* y,
+                         hipStream_t s) {
+  WideLayout w;
+  wide64_layout(sh, g, ws, &w);
+  ws.nseg = w.nseg;
+  return wide_format<4>(sh, g, dense, form, x, lopa_a, gate_w, w_up, w_down_t, t, w, y, s);
 }
 
 }  // namespace ffn

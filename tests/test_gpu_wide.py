@@ -51,6 +51,21 @@ def test_wide(gu, shape, dense):
     assert gu.rel_err(y, res.y) <= 3e-5
 
 
+# 33..64 tokens on d_ff whose segments of 64 rows fill the chip: 219 segments, 256, 448
+@pytest.mark.parametrize("dense", [False, True], ids=["sparse", "dense"])
+@pytest.mark.parametrize("shape", [(33, 72, 13957, 24, BF16, 1.6), (64, 136, 16384, 0, BF16, 2.0),
+                                   (49, 72, 28650, 40, BF16, 1.8), (64, 80, 14000, 16, I8, 1.6),
+                                   (50, 96, 14000, 0, I4, 1.6), (40, 16, 14000, 2048, BF16, 1.6)],
+                         ids=lambda s: "T%d_d%d_dff%d_r%d_w%d" % s[:5])
+def test_wide_33_to_64(gu, shape, dense):
+    T, d, d_ff, r, wdt, t = shape
+    inp = wl.make_inputs(605, T, d, d_ff, r=r, wdt=wdt)
+    y, idx, act, _ = (gu.run_gpu_q if wdt in (I8, I4) else gu.run_gpu)(gu.DevInputs(inp), t, dense=dense)
+    res = gu.run_oracle(inp, t, dense=dense)
+    gu.check_parity(res, y, idx, act, t, BF16, dense=dense, what=str(shape))
+    assert gu.rel_err(y, res.y) <= 3e-5
+
+
 @pytest.mark.parametrize("wdt", [BF16, I8], ids=["bf16", "i8"])
 @pytest.mark.parametrize("r", [0, 48], ids=["std", "lopa"])
 def test_wide_full_form(gu, wdt, r):
