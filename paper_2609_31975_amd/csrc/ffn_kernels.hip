@@ -736,8 +736,10 @@ __global__ __launch_bounds__(kBlock) void k_gate_up_t1(const float* __restrict__
     // x for the W_up dots (fp32 vectors, one row a wave): loaded once per workgroup, each
     // thread a share, ahead of the gate stream, and staged in LDS during the compaction, so
     // that the W_up rows go out right after it (every wave reading 16 KB of x there had put
-    // 50 MB of L2 reads in front of the 12 MB of W_up rows)
-    constexpr bool kXLds = !limb_vec<W, CPLU>() && CPLU <= 8 && !DENSE;
+    // 50 MB of L2 reads in front of the 12 MB of W_up rows).  Rows of more than 8 chunks a lane
+    // likewise: fp32 d 3840, d_ff 14231, r 480 24.6 -> 23.6 us a call, bf16 d 8192, d_ff 28672, r 1024
+    // 38.2 -> 37.0
+    constexpr bool kXLds = !limb_vec<W, CPLU>() && !DENSE;
     constexpr int XF4 = W::EPC / 4, kXF4 = kXLds ? CPLU * kWave * XF4 : kBlock, kXPT = kXF4 / kBlock;
     static_assert(kXPT * kBlock == kXF4, "x shares");
     __shared__ float4 s_xu[kXLds ? kXF4 : 1];
