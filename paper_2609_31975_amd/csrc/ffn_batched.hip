@@ -105,16 +105,30 @@ __device__ __forceinline__ void stage_rows(int* roff, int C, RowOf row_of) {  //
 //    planes [k step][token tile][lane] of uint4 (k_split_tokens); the lo plane starts
 //    part_bytes after the hi plane; tn = the planes' token-tile count.
 // fp32 weights: one piece instead of two, the chunk's 4 fp32 (one plane when PRE).
-template <int RT, int NT, int KU, int NP, class W = WBf16>
+// NORM (LoPA's z under RMSNorm): also the gains of the chunk's components.
+template <int RT, int NT, int KU, int NP, class W = WBf16, bool NORM = false>
 struct Frags {
   uint4 a[WStage<RT, KU, W>::NI];
   uint4 b[KU][NT][NP][is_f32<W>() ? 1 : 2];
+  uint4 gain[NORM ? KU : 1][is_f32<W>() ? 1 : 2];
 };
 
-template <int RT, int NT, int KU, int NP, bool PRE = false, class W = WBf16>
-__device__ __forceinline__ void load_frags(Frags<RT, NT, KU, NP, W>& f, const Buf& wb, int C,
+// RMSNorm between LoPA's factors inside the gate product: h = inv B (gain . z), inv = 1 /
+// sqrt(mean z^2 + eps) one scalar a token, so the product takes gain . z and its rows are scaled
+// afterwards.  sq[nt]: the sum of squares of the z components that this lane multiplies (token
+// 16 nt + (lane & 15)).  A kernel of its own for the norm had cost 4.5 us and a launch (8B shape, full
+// form, 16 tokens: 61.8 -> 58.9 us a call, the gate kernel 30.0 -> 31.1).
+template <int NT>
+struct ZNorm {
+  Buf gain;
+  bool has_gain;
+  float sq[NT];
+};
+
+template <int RT, int NT, int KU, int NP, bool PRE = false, class W = WBf16, bool NORM = false>
+__device__ __forceinline__ void load_frags(Frags<RT, NT, KU, NP, W, NORM>& f, const Buf& wb, int C,
                                            const int* roff, const Buf& tb, uint32_t part_bytes, int tn, int ks,
-                                           int ks1) {
+                                           int ks1, const ZNorm<NT>* zn = nullptr) {
   using S = WStage<RT, KU, W>;
   const int lane = lane_id(), m = lane & 15, g = lane >> 4;
   {
@@ -142,6 +156,11 @@ __device__ __forceinline__ void load_frags(Frags<RT, NT, KU, NP, W>& f, const Bu
   for (int u = 0; u < KU; ++u) {
     const int c = 4 * (ks + u) + g;
     const bool cv = ks + u < ks1 && c < C;
+    if constexpr (NORM) {
+      const uint32_t off = cv && zn->has_gain ? tok_bytes<W>() * (uint32_t)c : kOOB;
+      f.gain[u][0] = ldb(zn->gain, off);
+      if constexpr (!is_f32<W>()) f.gain[u][1] = ldb(zn->gain, off + 16);
+    }
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       const int tok = 16 * nt + m;
@@ -161,8 +180,7 @@ __device__ __forceinline__ void load_frags(Frags<RT, NT, KU, NP, W>& f, const Bu
 // The token fragment of one k step and token tile from fp32 rows: the NP copies of the
 // lane's 8 values summed, then split into hi / lo.
 template <int NP>
-__device__ __forceinline__ void sum_split(const uint4 (&b)[NP][2], bf16x8_t& hi, bf16x8_t& lo) {
-  float v[8];
+__device__ __forceinline__ void sum_copies(const uint4 (&b)[NP][2], float (&v)[8]) {
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const uint4 q = b[0][h];
@@ -181,11 +199,26 @@ __device__ __forceinline__ void sum_split(const uint4 (&b)[NP][2], bf16x8_t& hi,
       v[4 * h + 2] += __uint_as_float(q.z);
       v[4 * h + 3] += __uint_as_float(q.w);
     }
-  split8(v, hi, lo);
+}
+// One chunk of z under RMSNorm: its squares into sq, then times the gains.
+template <int E, int H>
+__device__ __forceinline__ void norm_chunk(float (&v)[E], const uint4 (&gain)[H], bool has_gain, float& sq) {
+#pragma unroll
+  for (int e = 0; e < E; ++e) sq = fmaf(v[e], v[e], sq);
+  if (has_gain) {
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      v[4 * h] *= __uint_as_float(gain[h].x);
+      v[4 * h + 1] *= __uint_as_float(gain[h].y);
+      v[4 * h + 2] *= __uint_as_float(gain[h].z);
+      v[4 * h + 3] *= __uint_as_float(gain[h].w);
+    }
+  }
 }
 
-template <int RT, int NT, int KU, int NP, bool PRE = false, class W = WBf16>
-__device__ __forceinline__ void mma_frags(const Frags<RT, NT, KU, NP, W>& f, uint4* tile, f32x4_t (&acc)[RT][NT]) {
+template <int RT, int NT, int KU, int NP, bool PRE = false, class W = WBf16, bool NORM = false>
+__device__ __forceinline__ void mma_frags(const Frags<RT, NT, KU, NP, W, NORM>& f, uint4* tile, f32x4_t (&acc)[RT][NT],
+                                          ZNorm<NT>* zn = nullptr) {
   using S = WStage<RT, KU, W>;
   const int lane = lane_id(), m = lane & 15, g = lane >> 4;
 #pragma unroll
@@ -216,6 +249,7 @@ __device__ __forceinline__ void mma_frags(const Frags<RT, NT, KU, NP, W>& f, uin
           v[2] += comp<2>(f.b[u][nt][p][0]);
           v[3] += comp<3>(f.b[u][nt][p][0]);
         }
+        if constexpr (NORM) norm_chunk(v, f.gain[u], zn->has_gain, zn->sq[nt]);
         uint4 a[RT];
         f32x4_t ks[RT];  // the k step's sums
 #pragma unroll
@@ -238,7 +272,10 @@ __device__ __forceinline__ void mma_frags(const Frags<RT, NT, KU, NP, W>& f, uin
         hi = bf8(f.b[u][nt][0][0]);
         lo = bf8(f.b[u][nt][0][1]);
       } else {
-        sum_split<NP>(f.b[u][nt], hi, lo);
+        float v[8];
+        sum_copies<NP>(f.b[u][nt], v);
+        if constexpr (NORM) norm_chunk(v, f.gain[u], zn->has_gain, zn->sq[nt]);
+        split8(v, hi, lo);
       }
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
@@ -263,23 +300,24 @@ __device__ __forceinline__ void mma_frags(const Frags<RT, NT, KU, NP, W>& f, uin
 // pair always multiplies both halves (a group past ks1 adds zeros) and the exit test
 // closes the pair, so no load sits on a conditional path: with an exit test between
 // the halves the compiler moved the loads next to their use and waited on them there.
-template <int RT, int NT, int KU, int NP, bool PRE = false, class W = WBf16>
+template <int RT, int NT, int KU, int NP, bool PRE = false, class W = WBf16, bool NORM = false>
 __device__ __forceinline__ void stream_rows(const Buf& wb, int C, const int* roff, uint4* tile, const Buf& tb,
-                                            uint32_t part_bytes, int tn, int ks0, int ks1, f32x4_t (&acc)[RT][NT]) {
+                                            uint32_t part_bytes, int tn, int ks0, int ks1, f32x4_t (&acc)[RT][NT],
+                                            ZNorm<NT>* zn = nullptr) {
   if (ks0 >= ks1) return;
-  Frags<RT, NT, KU, NP, W> f0, f1;
-  load_frags<RT, NT, KU, NP, PRE, W>(f0, wb, C, roff, tb, part_bytes, tn, ks0, ks1);
+  Frags<RT, NT, KU, NP, W, NORM> f0, f1;
+  load_frags<RT, NT, KU, NP, PRE, W, NORM>(f0, wb, C, roff, tb, part_bytes, tn, ks0, ks1, zn);
   if (ks0 + KU >= ks1) {  // a single group
-    mma_frags<RT, NT, KU, NP, PRE, W>(f0, tile, acc);
+    mma_frags<RT, NT, KU, NP, PRE, W, NORM>(f0, tile, acc, zn);
     return;
   }
   for (int ks = ks0;; ks += 2 * KU) {
-    load_frags<RT, NT, KU, NP, PRE, W>(f1, wb, C, roff, tb, part_bytes, tn, ks + KU, ks1);
+    load_frags<RT, NT, KU, NP, PRE, W, NORM>(f1, wb, C, roff, tb, part_bytes, tn, ks + KU, ks1, zn);
     issue_barrier();
-    mma_frags<RT, NT, KU, NP, PRE, W>(f0, tile, acc);
-    load_frags<RT, NT, KU, NP, PRE, W>(f0, wb, C, roff, tb, part_bytes, tn, ks + 2 * KU, ks1);
+    mma_frags<RT, NT, KU, NP, PRE, W, NORM>(f0, tile, acc, zn);
+    load_frags<RT, NT, KU, NP, PRE, W, NORM>(f0, wb, C, roff, tb, part_bytes, tn, ks + 2 * KU, ks1, zn);
     issue_barrier();
-    mma_frags<RT, NT, KU, NP, PRE, W>(f1, tile, acc);
+    mma_frags<RT, NT, KU, NP, PRE, W, NORM>(f1, tile, acc, zn);
     if (ks + 2 * KU >= ks1) break;
   }
 }
@@ -449,9 +487,11 @@ __device__ __forceinline__ void gate_up_body(const float* __restrict__ x, const 
   __shared__ uint32_t s_mask[kTiles];
   __shared__ int s_list[kSegRowsB];
   __shared__ int s_cnt;
+  __shared__ float s_zsq[HAS_G ? kParts : 1][16 * NT];  // sums of z^2 of the waves' k parts
 
   const int lane = lane_id(), wave = uniform(threadIdx.x / kWave);
   const int m = lane & 15, g = lane >> 4;
+  const bool norm = HAS_G && form.rms_eps > 0.f, has_g = HAS_G && form.g_idx;
   clear_output(y, T * d, meta, nseg);
   const TokSrc tok = token_source<W>(PRE, x, xs, Cu, T, ntt);
   const Buf ub = make_buf(w_up, 16u * (uint32_t)d_ff * (uint32_t)(Cu / R8));
@@ -476,8 +516,24 @@ __device__ __forceinline__ void gate_up_body(const float* __restrict__ x, const 
       const Buf gb = make_buf(gate_w, 16u * (uint32_t)d_ff * (uint32_t)(Cg / R8));
       if constexpr (LOPA) {
         const uint32_t part = tok_bytes<W>() * (uint32_t)tc * (uint32_t)Cg;
-        stream_rows<kTiles, NT, KU, 2, false, W>(gb, Cg, roff, s_stage[wave], make_buf(zp, 2 * part), part, T, ks0,
-                                                 ks1, acc);
+        ZNorm<NT> zn;
+        if constexpr (HAS_G) {
+          zn.has_gain = norm && form.rms_gain;
+          zn.gain = make_buf(form.rms_gain, tok_bytes<W>() * (uint32_t)Cg);
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) zn.sq[nt] = 0.f;
+        }
+        stream_rows<kTiles, NT, KU, 2, false, W, HAS_G>(gb, Cg, roff, s_stage[wave], make_buf(zp, 2 * part), part, T,
+                                                        ks0, ks1, acc, &zn);
+        if constexpr (HAS_G) {
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) {
+            float q = zn.sq[nt];
+            q += __shfl_xor(q, 16);
+            q += __shfl_xor(q, 32);
+            if (lane < 16) s_zsq[wave][16 * nt + lane] = q;
+          }
+        }
       } else {
         stream_rows<kTiles, NT, KU, 1, PRE, W>(gb, Cg, roff, s_stage[wave], tok.b, tok.part, tok.tn, ks0, ks1, acc);
       }
@@ -493,7 +549,7 @@ __device__ __forceinline__ void gate_up_body(const float* __restrict__ x, const 
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int tok = 16 * nt + m, rl = 16 * wave + 4 * g + i;
-          gxb[nt][i] = ldb32(xb, tok < T && rl < nrows ? 4u * ((uint32_t)tok * (uint32_t)d_ff + (uint32_t)(row0 + rl))
+          gxb[nt][i] = ldb32(xb, has_g && tok < T && rl < nrows ? 4u * ((uint32_t)tok * (uint32_t)d_ff + (uint32_t)(row0 + rl))
                                                         : kOOB);
         }
     }
@@ -519,6 +575,15 @@ __device__ __forceinline__ void gate_up_body(const float* __restrict__ x, const 
       for (int nt = 0; nt < NT; ++nt)
         h[nt] = ((s_red[0][wave][nt][lane] + s_red[1][wave][nt][lane]) + s_red[2][wave][nt][lane]) +
                 s_red[3][wave][nt][lane];
+      float inv[HAS_G ? NT : 1];
+      if constexpr (HAS_G) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const int o = 16 * nt + m;
+          const float q = ((s_zsq[0][o] + s_zsq[1][o]) + s_zsq[2][o]) + s_zsq[3][o];
+          inv[nt] = norm ? 1.f / sqrtf(q / (float)(Cg * tile_elems<W>()) + form.rms_eps) : 1.f;
+        }
+      }
       uint32_t mask = 0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -529,6 +594,7 @@ __device__ __forceinline__ void gate_up_body(const float* __restrict__ x, const 
           const int tok = 16 * nt + m;
           float hv = h[nt][i];
           if constexpr (Q) hv *= __builtin_bit_cast(float, sgb[i]);
+          if constexpr (HAS_G) hv *= inv[nt];
           if constexpr (HAS_G) hv += __builtin_bit_cast(float, gxb[nt][i]);  // h += G x
           const bool on = tok < T && hv > t;
           if (tok < T && rl < nrows) s_act[rl][tok] = on ? (FULL ? gate_value(form.act, hv - t) : hv - t) : 0.f;
@@ -866,6 +932,8 @@ __global__ __launch_bounds__(kQ4Threads) void k_gate_up_q4(FFN_GATE_UP_PARAMS) {
   __shared__ float s_act[kSegRowsB][4];
   __shared__ int s_list[kSegRowsB];
   __shared__ int s_cnt;
+  __shared__ float s_zsq[HAS_G ? kQ4Waves : 1][4];  // sums of z^2 of the waves' shares
+  const bool norm = HAS_G && form.rms_eps > 0.f, has_g = HAS_G && form.g_idx;
 
   const int lane = lane_id(), wave = uniform(threadIdx.x / kWave);
   for (int j = blockIdx.x * kQ4Threads + threadIdx.x; j < T * d; j += gridDim.x * kQ4Threads) y[j] = 0.f;
@@ -908,6 +976,33 @@ __global__ __launch_bounds__(kQ4Threads) void k_gate_up_q4(FFN_GATE_UP_PARAMS) {
         q4_load_tokens<W, UX>(x, T, d, Kpx, d, vx);
         float4 vz[UZ][2];
         if constexpr (LOPA) q4_load_tokens<W, UZ>(zp, T, Cg * TE, Kpz, Cg * TE, vz, 2, (uint32_t)(tc * Cg * TE));
+        if constexpr (HAS_G) {  // squares and gains of this thread's components of z (token threadIdx.x % 4)
+          float4 gn[UZ][2];
+          const bool has_gain = norm && form.rms_gain;
+          const Buf nb = make_buf(form.rms_gain, 4u * (uint32_t)(Cg * TE));
+          float sq = 0.f;
+#pragma unroll
+          for (int u = 0; u < UZ; ++u) {
+            const int k = 8 * (((int)threadIdx.x + u * kQ4Threads) / 4);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              gn[u][h] = __builtin_bit_cast(float4, ldb(nb, has_gain && k + 4 * h < Cg * TE ? 4u * (uint32_t)(k + 4 * h) : kOOB));
+              const float4 z = vz[u][h];
+              sq = fmaf(z.x, z.x, fmaf(z.y, z.y, fmaf(z.z, z.z, fmaf(z.w, z.w, sq))));
+            }
+          }
+          if (has_gain) {
+#pragma unroll
+            for (int u = 0; u < UZ; ++u)
+#pragma unroll
+              for (int h = 0; h < 2; ++h)
+                vz[u][h] = make_float4(vz[u][h].x * gn[u][h].x, vz[u][h].y * gn[u][h].y, vz[u][h].z * gn[u][h].z,
+                                       vz[u][h].w * gn[u][h].w);
+          }
+#pragma unroll
+          for (int o = 4; o < kWave; o <<= 1) sq += __shfl_xor(sq, o);
+          if (lane < 4) s_zsq[wave][lane] = sq;
+        }
         q4_store_tokens<W, UX>(vx, Kpx, s_tok);
         if constexpr (LOPA) q4_store_tokens<W, UZ>(vz, Kpz, tok_g);
         __syncthreads();
@@ -928,7 +1023,7 @@ __global__ __launch_bounds__(kQ4Threads) void k_gate_up_q4(FFN_GATE_UP_PARAMS) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
           gxv[j] = __int_as_float(
-              ldb32(xb, j < T && lane < nrows ? 4u * ((uint32_t)j * (uint32_t)d_ff + (uint32_t)(row0 + lane)) : kOOB));
+              ldb32(xb, has_g && j < T && lane < nrows ? 4u * ((uint32_t)j * (uint32_t)d_ff + (uint32_t)(row0 + lane)) : kOOB));
       }
     __syncthreads();
     if (wave == 0) {
@@ -941,6 +1036,13 @@ __global__ __launch_bounds__(kQ4Threads) void k_gate_up_q4(FFN_GATE_UP_PARAMS) {
 #pragma unroll
         for (int w = 0; w < kQ4Waves; ++w) hv += s_pg[w][q][j][i];
         if constexpr (Q) hv *= sg;
+        if constexpr (HAS_G)
+          if (norm) {
+            float q = 0.f;
+#pragma unroll
+            for (int w = 0; w < kQ4Waves; ++w) q += s_zsq[w][j];
+            hv *= 1.f / sqrtf(q / (float)(Cg * TE) + form.rms_eps);
+          }
         if constexpr (HAS_G) hv += gxv[j];
         const bool on = j < T && hv > t;
         if (lane < nrows) s_act[lane][j] = on ? (FULL ? gate_value(form.act, hv - t) : hv - t) : 0.f;
@@ -1423,9 +1525,8 @@ hipError_t gate_nt(const Shape& sh, const Form& f, const float* x, const void* g
 template <class W, bool LOPA, bool DENSE>
 hipError_t gate_form(const Shape& sh, const Form& f, const float* x, const void* gate_w, const void* w_up, float t,
                      Workspace& ws, float* y, hipStream_t s) {
-  // the norm runs before this kernel, so only G needs the LoPA form here
   if constexpr (LOPA)
-    if (f.g_idx) return gate_nt<W, LOPA, DENSE, kFormLoPA>(sh, f, x, gate_w, w_up, t, ws, y, s);
+    if (f.kind() == kFormLoPA) return gate_nt<W, LOPA, DENSE, kFormLoPA>(sh, f, x, gate_w, w_up, t, ws, y, s);
   return f.full() ? gate_nt<W, LOPA, DENSE, kFormAct>(sh, f, x, gate_w, w_up, t, ws, y, s)
                   : gate_nt<W, LOPA, DENSE, kFormDefault>(sh, f, x, gate_w, w_up, t, ws, y, s);
 }
@@ -1468,10 +1569,6 @@ hipError_t batched_format(const Shape& sh, Gate g, bool dense, const Form& form,
     // pre-split tokens (more than 16): one token tile a workgroup
     e = sh.T <= 16 ? z_mfma<W, 1, false>(sh, form, x, lopa_a, ws, s) : z_mfma<W, 1, true>(sh, form, x, lopa_a, ws, s);
     if (e != hipSuccess) return e;
-    // RMSNorm between A and B: the two partial copies of z become one normalised copy
-    if (form.rms_eps > 0.f &&
-        (e = launch_rms_norm(ws.z, 2, ws.tc, sh.T, sh.r, form.rms_gain, form.rms_eps, s)) != hipSuccess)
-      return e;
   }
   if (lopa)
     e = dense ? gate_form<W, true, true>(sh, form, x, gate_w, w_up, t, ws, y, s)

@@ -151,7 +151,7 @@ bool lopa_fuses_z(const Shape& sh, const Form& form);
 // the whole call (LoPA z, gate + union + W_up, down), clearing y first.
 bool batched_ok(const Shape& sh, Gate g);
 int batched_segments(int d_ff);
-// form.rms_eps > 0: RMSNorm on z between the LoPA factors.
+// form.rms_eps > 0: RMSNorm on z between the LoPA factors, inside the gate kernels.
 hipError_t launch_batched(const Shape& sh, Gate g, bool dense, const Form& form, const float* x,
                           const void* lopa_a, const void* gate_w, const void* w_up, const void* w_down_t, float t,
                           Workspace& ws, float* y, hipStream_t s);
