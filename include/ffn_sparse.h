@@ -199,7 +199,7 @@ typedef struct {
  * scales struct or array, FFN_ERR_ALIGN for a misaligned scale array, FFN_ERR_OPTION for
  * scales with fp32 / bf16 weights.  Quantized weights take the single-token kernels
  * (T = 1, d a multiple of 16 (int8) or 32 (int4), up to 8192), the matrix-core batch
- * kernels (2..64 tokens a pass, d and r multiples of 16 / 32; the codes enter the bf16
+ * kernels (2 tokens and more, d and r multiples of 16 / 32; the codes enter the bf16
  * products unchanged, being small integers) or the element-wise kernels (any other shape).
  * The single-token kernels form their dot products with the integer dot instructions
  * against a 24-bit fixed-point copy of x (or z): relative to the vector's largest
@@ -227,15 +227,15 @@ int ffn_lopa_dense_forward_q(ffn_dtype_t wdt, int T, int d, int d_ff, int r, con
  *   act_host        [T][d_ff] fp32 (may be NULL): act_host[tau][k] = the activation value
  *                   (h - t for the default form) of neuron idx_host[k] for token tau, or 0
  *                   where that token is inactive
- * For a dense call every neuron is listed.  T is at most 64: a larger call runs as passes of
- * 64 tokens, and the workspace keeps the lists of its last pass only (FFN_ERR_SHAPE).
+ * For a dense call every neuron is listed.  T is at most 64: a larger call runs as passes of up to
+ * 64 tokens or more (as many as its workspace holds), whose lists are not kept (FFN_ERR_SHAPE).
  * Returns FFN_OK or an error code. */
 int ffn_active_set(const void* ws, int T, int d, int d_ff, int r, int32_t* n_union, int32_t* idx_host,
                    float* act_host, hipStream_t stream);
 
 /* The active set of the last forward call as DEVICE pointers into the workspace (the
  * compaction of Section 3.1's skip rule; calls of T <= 64 tokens, FFN_ERR_SHAPE above, since
- * larger batches run in passes of 64 that reuse the workspace).  Pure pointer arithmetic on the
+ * larger batches run in passes that reuse the workspace).  Pure pointer arithmetic on the
  * host: nothing is enqueued, read or synchronized, so it may be called at any time, also
  * while a stream is being captured into a graph; the data behind the pointers is valid once
  * the forward call's work on its stream has completed, and device work ordered after the call

@@ -48,7 +48,6 @@ namespace {
 constexpr int kTiles = 4;                // 16-row tiles of a gate segment
 constexpr int kSegRowsB = 16 * kTiles;   // rows per gate segment (one 64-lane ballot)
 constexpr int kParts = kBlock / kWave;   // k parts of a workgroup, one per wave
-constexpr int kSegQuads = kSegRowsB / 4; // union entries go to the down kernel by quads
 constexpr int kSegGrid = 256;            // most workgroups of the gate kernel, one per CU
 constexpr int kSegGrid2 = 512;           // the same at two workgroups per CU
 
@@ -450,8 +449,8 @@ __device__ __forceinline__ void put_alive(uint16_t* out, const bool (&nz)[4]) {
 // wave w owning tile w.  A neuron joins the union if any token activates it (h > t;
 // NaN compares false); one ballot orders the union ascending.  The W_up dots of the
 // union rows use the same split, and zval = act * v goes to the buffer of the down kernel by
-// quads of entries: quad 16 seg + k (entries 4 k .. 4 k + 3 of segment seg), token tile nt and
-// token 16 nt + m at uint4 ((16 seg + k) ntt + nt) 16 + m, the four values as bf16 hi parts then
+// quads of entries: quad qps seg + k (entries 4 k .. 4 k + 3 of segment seg), token tile nt and
+// token 16 nt + m at uint4 ((qps seg + k) ntt + nt) 16 + m, the four values as bf16 hi parts then
 // lo parts (fp32 weights: as fp32).  A used quad is written whole (zero past the union), an
 // unused one is never read.
 // fp32 weights also leave alive[4 seg + k], bit j: entry 16 k + j of the segment has a value other
@@ -471,7 +470,7 @@ __device__ __forceinline__ void gate_up_body(const float* __restrict__ x, const 
                                              const uint4* __restrict__ xs, int ntt, Form form,
                                              const float* __restrict__ gx, const float* __restrict__ s_g,
                                              const float* __restrict__ s_up, const float* __restrict__ s_down,
-                                             uint16_t* __restrict__ alive) {
+                                             uint16_t* __restrict__ alive, int qps) {
   constexpr bool Q = is_quant<W>();
   constexpr int R8 = W::EPC / tile_elems<W>();
   constexpr bool FULL = FORM != kFormDefault, HAS_G = FORM == kFormLoPA;
@@ -703,7 +702,7 @@ __device__ __forceinline__ void gate_up_body(const float* __restrict__ x, const 
             hw[i >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, hb) << (16 * (i & 1));
             lw[i >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, lb) << (16 * (i & 1));
           }
-          zf[(((size_t)seg * kSegQuads + 4 * wave + g) * ntt + nt) * 16 + m] =
+          zf[(((size_t)seg * qps + 4 * wave + g) * ntt + nt) * 16 + m] =
               is_f32<W>() ? __builtin_bit_cast(uint4, zv) : make_uint4(hw[0], hw[1], lw[0], lw[1]);
         }
       }
@@ -718,10 +717,10 @@ __device__ __forceinline__ void gate_up_body(const float* __restrict__ x, const 
       int32_t *__restrict__ meta, int32_t *__restrict__ seg_count, int32_t *__restrict__ seg_idx,                  \
       float *__restrict__ seg_act, uint4 *__restrict__ zf, float *__restrict__ y, const uint4 *__restrict__ xs,  \
       int ntt, Form form, const float *__restrict__ gx, const float *__restrict__ s_g,                            \
-      const float *__restrict__ s_up, const float *__restrict__ s_down, uint16_t *__restrict__ alive
+      const float *__restrict__ s_up, const float *__restrict__ s_down, uint16_t *__restrict__ alive, int qps
 #define FFN_GATE_UP_ARGS                                                                                            \
   x, zp, gate_w, Cg, w_up, Cu, T, d, d_ff, nseg, t, slots, tc, meta, seg_count, seg_idx, seg_act, zf, y, xs, ntt, form, \
-      gx, s_g, s_up, s_down, alive
+      gx, s_g, s_up, s_down, alive, qps
 
 // One workgroup per CU: four k steps a group for one token tile (two for LoPA's short
 // gate rows and for wider token tiles; one for LoPA's gate rows with four token tiles,
@@ -1111,7 +1110,7 @@ __global__ __launch_bounds__(kQ4Threads) void k_gate_up_q4(FFN_GATE_UP_PARAMS) {
         hw[i >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, hb) << (16 * (i & 1));
         lw[i >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, lb) << (16 * (i & 1));
       }
-      zf[((size_t)seg * kSegQuads + qq) * ntt * 16 + m] =
+      zf[((size_t)seg * qps + qq) * ntt * 16 + m] =
           is_f32<W>() ? __builtin_bit_cast(uint4, zv) : make_uint4(hw[0], hw[1], lw[0], lw[1]);
     }
     if constexpr (is_f32<W>())
@@ -1282,14 +1281,15 @@ __device__ __forceinline__ void dn_mma(const DnFrags<NT, W>& f, uint4* tile,
 template <int NT, class W>
 __global__ __launch_bounds__(kBlock) void k_down_mfma(const int32_t* __restrict__ seg_count,
                                                       const int32_t* __restrict__ seg_idx,
-                                                      const uint4* __restrict__ zf, int nseg, int d_ff, int R, int tc,
+                                                      const uint4* __restrict__ zf, int nseg, int qps, int d_ff,
+                                                      int R, int tc,
                                                       const uint4* __restrict__ w_down_t, int C, int d, int T,
                                                       float* __restrict__ y, const uint2* __restrict__ alive) {
   using K = DnCfg<NT, W>;
   constexpr int CW = K::CW, GS = kParts / CW, WCOLS = K::WCOLS;
   const Buf db = make_buf(w_down_t, 16u * (uint32_t)d_ff * (uint32_t)C);
   const int ntt = (tc + 15) / 16;
-  const Buf zb = make_buf(zf, 4096u * (uint32_t)nseg * (uint32_t)ntt);
+  const Buf zb = make_buf(zf, 256u * (uint32_t)(nseg * qps) * (uint32_t)ntt);
   // LDS: the waves' tiles and the chunk's packed list during the loop; afterwards the
   // same space holds every wave's sums, [wave][ct][h][nt][lane] as f32x4
   constexpr int STAGE_U4 = kParts * 32 * K::PITCH, IDX_U4 = (kDnList + kDnList / 4 + 3) / 4;
@@ -1363,7 +1363,7 @@ __global__ __launch_bounds__(kBlock) void k_down_mfma(const int32_t* __restrict_
           bool read = lane < n;
           if constexpr (K::F32) read = read && (((lane < 32 ? s_alive[sg].x : s_alive[sg].y) >> (lane & 31)) & 1u);
           s_row[o] = read ? v0[u] : -1;
-          if ((lane & 3) == 0) s_zq[o >> 2] = kSegQuads * (seg_lo + sg) + (lane >> 2);
+          if ((lane & 3) == 0) s_zq[o >> 2] = qps * (seg_lo + sg) + (lane >> 2);
         }
       }
     }
@@ -1467,12 +1467,21 @@ hipError_t z_mfma(const Shape& sh, const Form& form, const float* x, const void*
   return hipGetLastError();
 }
 
-// Row-balanced segments of at most 64 rows; beyond 128 of them the count is a multiple
-// of the gate kernel's grid so that every workgroup gets the same number.
-int segments_for(int d_ff, int grid) {
+// Row-balanced segments: of at most 64 rows where there are more than 128 of those, in multiples of
+// the gate kernel's grid so that every workgroup gets the same number; of a smaller d_ff at most 32
+// rows, which reach twice the compute units (90%, calls: bf16 d 2560, d_ff 8100, 16 tokens 41.7 -> 36.5
+// us; int8 d 2048, d_ff 7000, 16 tokens 31.4 -> 29.0; fp32 d 2048, d_ff 7000, r 256, 16 tokens 42.9 ->
+// 37.5; bf16 d 1024, d_ff 4000, 32 tokens 27.3 -> 24.7, 8 tokens 18.6 -> 19.7).  The 4x4x4 kernel, whose
+// workgroups each stage all tokens, keeps 64 rows up to half of that d_ff (int8 d 1024, d_ff 4000,
+// r 128, 4 tokens 21.5 us against 22.6 with 32).
+constexpr int kSmallDff = 128 * kSegRowsB;
+int segments_for(int d_ff, int grid, bool q4 = false) {
   const int n = (d_ff + kSegRowsB - 1) / kSegRowsB;
-  return n > 128 ? (n + grid - 1) / grid * grid : n;
+  if (d_ff > kSmallDff) return (n + grid - 1) / grid * grid;
+  return q4 && d_ff <= kSmallDff / 2 ? n : (d_ff + 31) / 32;
 }
+// zval quads a segment has room for: those of its rows.  nseg seg_quads <= 16 batched_segments(d_ff).
+int seg_quads(int d_ff, int nseg) { return ((d_ff + nseg - 1) / nseg + 3) / 4; }
 
 // The 4x4x4 kernel takes batches of at most four tokens whose rows (and LoPA's r), padded to
 // a whole step, fit its token LDS.
@@ -1488,20 +1497,23 @@ hipError_t gate_mfma(const Shape& sh, const Form& form, const float* x, const vo
   const int Cu = sh.d / tile_elems<W>(), Cg = LOPA ? sh.r / tile_elems<W>() : Cu;
   if constexpr (NT == 1)
     if (q4_fits<W>(sh, LOPA)) {
-      ws.nseg = segments_for(sh.d_ff, kSegGrid);
+      ws.nseg = segments_for(sh.d_ff, kSegGrid, true);
       return launch_gate_kernel_n(k_gate_up_q4<W, LOPA, DENSE, FORM>, ws.nseg < kSegGrid ? ws.nseg : kSegGrid,
                                   kQ4Threads, s, x,
                                 (const float*)ws.z, static_cast<const uint4*>(gate_w), Cg,
                                 static_cast<const uint4*>(w_up), Cu, sh.T, sh.d, sh.d_ff, ws.nseg, t, ws.slots, ws.tc,
                                 ws.meta, ws.seg_count, ws.seg_idx, ws.seg_act, ws.zf, y, ws.xs, token_tiles(ws), form,
-                                (const float*)ws.gx, LOPA ? sh.sc.b : sh.sc.gate, sh.sc.up, sh.sc.down, alive_masks(ws));
+                                (const float*)ws.gx, LOPA ? sh.sc.b : sh.sc.gate, sh.sc.up, sh.sc.down, alive_masks(ws), seg_quads(sh.d_ff, ws.nseg));
     }
-  // two workgroups a CU only where their segments stay near 64 rows: halving 8B-shaped
-  // segments to 28 rows left the row tiles half empty (int8 / int4 at four tokens: 52.7 /
-  // 54.4 us a call, 42.1 / 41.9 us with one workgroup a CU).  On the 70B shape LoPA gains
-  // too (eight tokens: gate kernel 76.1 -> 71.1 us), where one workgroup a CU walks two
-  // segments one after the other.
-  const bool two = NT == 1 && sh.d_ff >= 48 * kSegGrid2;
+  // The two-workgroup kernel (two k steps a load group) takes segments that stay near 64 rows,
+  // d_ff >= 24576: halving 8B-shaped bf16 / int8 / int4 segments to 28 rows left the row tiles half empty
+  // (int8 / int4 at four tokens, on these kernels: 52.7 / 54.4 us a call, 42.1 / 41.9 us with one
+  // workgroup a CU); on the 70B shape LoPA gains too (eight tokens: gate kernel 76.1 -> 71.1 us), where
+  // one workgroup a CU walks two segments one after the other.  fp32 rows, twice as long, gain from
+  // it at any d_ff (d 3840, d_ff 14231, r 480, 5 / 8 / 16 tokens 73.7 / 83.0 / 90.7 -> 67.8 / 77.5 / 91.1
+  // us), and so does a d_ff whose segments are one a workgroup (bf16 d 1024, d_ff 4000, 8 tokens 22.1 ->
+  // 18.6; d 4608, d_ff 8000, r 512, 3 tokens 42.1 -> 37.0).
+  const bool two = NT == 1 && (is_f32<W>() || sh.d_ff <= kSmallDff || sh.d_ff >= 48 * kSegGrid2);
   const int grid = two ? kSegGrid2 : kSegGrid;
   ws.nseg = segments_for(sh.d_ff, grid);
   const int g = ws.nseg < grid ? ws.nseg : grid;
@@ -1511,7 +1523,7 @@ hipError_t gate_mfma(const Shape& sh, const Form& form, const float* x, const vo
   return launch_gate_kernel(kernel, g, s, x, (const float*)ws.z, static_cast<const uint4*>(gate_w), Cg,
                             static_cast<const uint4*>(w_up), Cu, sh.T, sh.d, sh.d_ff, ws.nseg, t, ws.slots, ws.tc,
                             ws.meta, ws.seg_count, ws.seg_idx, ws.seg_act, ws.zf, y, ws.xs, token_tiles(ws), form,
-                            (const float*)ws.gx, LOPA ? sh.sc.b : sh.sc.gate, sh.sc.up, sh.sc.down, alive_masks(ws));
+                            (const float*)ws.gx, LOPA ? sh.sc.b : sh.sc.gate, sh.sc.up, sh.sc.down, alive_masks(ws), seg_quads(sh.d_ff, ws.nseg));
 }
 
 template <class W, bool LOPA, bool DENSE, int FORM>
@@ -1552,7 +1564,8 @@ hipError_t down_mfma(const Shape& sh, const void* w_down_t, const Workspace& ws,
   const int64_t rows_per_seg = (sh.d_ff + ws.nseg - 1) / ws.nseg;
   while (R < ws.nseg && ((ws.nseg + R - 1) / R) * rows_per_seg > kDnSlots) ++R;
   if (((ws.nseg + R - 1) / R) * rows_per_seg > kDnSlots || S * R > INT32_MAX) return hipErrorInvalidValue;
-  k_down_mfma<NT, W><<<(int)(S * R), kBlock, 0, s>>>(ws.seg_count, ws.seg_idx, ws.zf, ws.nseg, sh.d_ff, (int)R,
+  k_down_mfma<NT, W><<<(int)(S * R), kBlock, 0, s>>>(ws.seg_count, ws.seg_idx, ws.zf, ws.nseg,
+                                                     seg_quads(sh.d_ff, ws.nseg), sh.d_ff, (int)R,
                                                      ws.tc, static_cast<const uint4*>(w_down_t), C, sh.d, sh.T, y,
                                                      reinterpret_cast<const uint2*>(alive_masks(ws)));
   return hipGetLastError();
@@ -1605,7 +1618,9 @@ bool batched_ok(const Shape& sh, Gate g) {
 }
 
 // the most segments any gate kernel of this path uses (workspace sizing)
-int batched_segments(int d_ff) { return segments_for(d_ff, kSegGrid2); }
+int batched_segments(int d_ff) {
+  return d_ff > kSmallDff ? segments_for(d_ff, kSegGrid2) : (d_ff + kSegRowsB - 1) / kSegRowsB;
+}
 
 hipError_t launch_split_tokens(const Shape& sh, const float* x, const Workspace& ws, hipStream_t s) {
   return split_tokens<false>(sh, x, ws, s);
