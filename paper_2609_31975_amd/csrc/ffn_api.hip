@@ -57,6 +57,11 @@ size_t workspace_layout(int T, int d, int d_ff, int r, void* base, Workspace* ou
   return off;
 }
 
+// Bytes in front of seg_count: meta and the z slots, which a wide pass leaves as they are.
+size_t pass_head(const Workspace& ws, const void* base) {
+  return (size_t)(reinterpret_cast<const char*>(ws.seg_count) - static_cast<const char*>(base));
+}
+
 namespace {
 
 bool aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -161,17 +166,14 @@ int run(const Call& c) {
   if (c.ws_bytes < workspace_layout(c.T, c.d, c.d_ff, c.r, c.ws, &ws)) return FFN_ERR_WORKSPACE;
 
   const Gate g = lopa ? Gate::LoPA : Gate::Standard;
-  // Tokens run in passes; each pass is an independent FFN call.  More than kTokChunk tokens take
-  // equal passes (in whole token tiles) of as many as the wide kernels have workspace for, else,
-  // and for a last pass of at most kTokChunk, passes of up to kTokChunk.
+  // Tokens run in passes; each pass is an independent FFN call.  More than kTokChunk tokens take the
+  // wide kernels' passes where those have workspace for them; else, and for a last pass of at most
+  // kTokChunk, passes of up to kTokChunk.
   int per = kTokChunk;
-  const size_t head = reinterpret_cast<char*>(ws.seg_count) - static_cast<char*>(c.ws);  // meta and z slots stay
+  const size_t head = pass_head(ws, c.ws);
   if (c.T > kTokChunk) {
-    const int most = wide_pass_tokens(Shape{c.T, c.d, c.d_ff, c.r, (int)c.wdt, scales}, g, form, head, c.ws_bytes);
-    if (most > 0) {
-      const int n = (c.T + most - 1) / most;
-      per = ((c.T + n - 1) / n + 15) / 16 * 16;
-    }
+    const int wide = wide_pass_tokens(Shape{c.T, c.d, c.d_ff, c.r, (int)c.wdt, scales}, g, form, head, c.ws_bytes);
+    if (wide > 0) per = wide;
   }
   for (int t0 = 0; t0 < c.T; t0 += per) {
     Shape sh{c.T - t0 < per ? c.T - t0 : per, c.d, c.d_ff, c.r, (int)c.wdt, scales};
@@ -179,7 +181,8 @@ int run(const Call& c) {
     float* y = c.y + (size_t)t0 * c.d;
     hipError_t e = hipSuccess;
     if (sh.T > kTokChunk) {
-      e = launch_wide(sh, g, c.dense, form, x, c.lopa_a, c.gate, c.w_up, c.w_down_t, c.t, c.ws, head, y, c.stream);
+      e = launch_wide(sh, g, c.dense, form, x, c.lopa_a, c.gate, c.w_up, c.w_down_t, c.t, c.ws, head, c.ws_bytes, y,
+                      c.stream);
     } else if (batched_ok(sh, g)) {
       e = launch_batched(sh, g, c.dense, form, x, c.lopa_a, c.gate, c.w_up, c.w_down_t, c.t, ws, y, c.stream);
     } else {

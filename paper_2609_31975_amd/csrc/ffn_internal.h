@@ -76,6 +76,7 @@ struct Workspace {
 };
 
 size_t workspace_layout(int T, int d, int d_ff, int r, void* base, Workspace* out);
+size_t pass_head(const Workspace& ws, const void* base);
 
 // Kernel launch parameters decided on the host.
 // Row scales of quantized weights (FFN_I8 / FFN_I4): one fp32 per stored matrix row; all
@@ -159,13 +160,15 @@ hipError_t launch_batched(const Shape& sh, Gate g, bool dense, const Form& form,
 // The tokens' bf16 hi / lo fragment planes into ws.xs.
 hipError_t launch_split_tokens(const Shape& sh, const float* x, const Workspace& ws, hipStream_t s);
 
-// Calls of more than kTokChunk tokens (ffn_wide.hip): tokens of a pass (0: the path does not take the
-// call), and a pass of sh.T of them.  Its regions start `head` bytes into the workspace of `bytes`.
+// Calls of more than kTokChunk tokens (ffn_wide.hip): tokens of the call's passes (0: the path does not
+// take the call), the workspace that a pass of sh.T tokens uses, and the pass.  Its regions start
+// `head` bytes into the workspace of `bytes`.
 constexpr int kWidePass = 512;
+size_t wide_pass_bytes(const Shape& sh, Gate g, const Form& form, size_t head);
 int wide_pass_tokens(const Shape& sh, Gate g, const Form& form, size_t head, size_t bytes);
 hipError_t launch_wide(const Shape& sh, Gate g, bool dense, const Form& form, const float* x, const void* lopa_a,
                        const void* gate_w, const void* w_up, const void* w_down_t, float t, void* base, size_t head,
-                       float* y, hipStream_t s);
+                       size_t bytes, float* y, hipStream_t s);
 // A pass of kWide64Min .. kTokChunk tokens on the same kernels, in the workspace's own regions.
 constexpr int kWide64Min = 33;
 bool wide64_ok(const Shape& sh, Gate g, const Workspace& ws);

@@ -907,9 +907,29 @@ hipError_t wide_format(const Shape& sh, Gate g, bool dense, const Form& form, co
 
 }  // namespace
 
-// Tokens of a pass: the most (a multiple of 16, at most kWidePass) whose regions fit `bytes` of
-// workspace, or 0 if the path does not take the call: 65 tokens or more, bf16 or quantized rows
-// that the 2..64-token kernels take, and every byte offset below 2^31.
+// Bytes of workspace that a pass of sh.T tokens uses, `head` included.
+size_t wide_pass_bytes(const Shape& sh, Gate g, const Form& form, size_t head) {
+  return wide_layout(sh.T, sh.d, sh.d_ff, g == Gate::LoPA ? sh.r : 0, form.g_idx != nullptr, nullptr, head, nullptr);
+}
+
+namespace {
+// A pass's regions fit `bytes` of workspace and every byte offset is below 2^31.
+bool wide_pass_fits(const Shape& sh, Gate g, const Form& form, size_t head, size_t bytes) {
+  const int64_t lim = int64_t(1) << 31;
+  const int r = g == Gate::LoPA ? sh.r : 0;
+  WideLayout w;
+  return wide_layout(sh.T, sh.d, sh.d_ff, r, form.g_idx != nullptr, nullptr, head, &w) <= bytes &&
+         256 * (int64_t)w.nseg * w.qps * kWTiles < lim && 4 * (int64_t)sh.T * sh.d < lim / 4 &&
+         4 * (int64_t)sh.T * (r > 0 ? r : 1) < lim / 4;
+}
+}  // namespace
+
+// Tokens of the passes of a call of sh.T: as few equal passes (in whole token tiles, of at most
+// kWidePass) as have room for their regions in `bytes` of workspace, or 0 if the path does not take
+// the call: 65 tokens or more a pass, bf16 or quantized rows that the 2..64-token kernels take.  A
+// last pass of fewer tokens than the others is checked by itself: a layout need not shrink with its
+// tokens (fewer blocks can mean smaller segments and so fewer zval quads, and z's copies then a
+// region of their own).
 // Passes of 64 against one pass here, 90%: 8B shape LoPA r = 512, 65 / 96 / 128 / 200 / 256 tokens
 // 118.8 / 171.7 / 199.5 / 345.6 / 398.6 -> 110.5 / 117.9 / 124.0 / 158.6 / 167.2 us; d 512, d_ff 2000,
 // 100 tokens 51.8 -> 37.8; 70B shape LoPA r = 1024, 100 tokens 639.8 -> 329.1.  65 tokens is the
@@ -919,24 +939,24 @@ int wide_pass_tokens(const Shape& sh, Gate g, const Form& form, size_t head, siz
   Shape one = sh;
   one.T = kTokChunk;
   if (!batched_ok(one, g)) return 0;
-  const int64_t lim = int64_t(1) << 31;
-  const int r = g == Gate::LoPA ? sh.r : 0;
-  for (int t = kWidePass; t > kTokChunk; t -= 16) {
-    WideLayout w;
-    if (wide_layout(t, sh.d, sh.d_ff, r, form.g_idx != nullptr, nullptr, head, &w) > bytes) continue;
-    if (256 * (int64_t)w.nseg * w.qps * kWTiles >= lim || 4 * (int64_t)t * sh.d >= lim / 4 ||
-        4 * (int64_t)t * (r > 0 ? r : 1) >= lim / 4)
-      continue;
-    return t;
+  for (int n = (sh.T + kWidePass - 1) / kWidePass;; ++n) {
+    const int per = ((sh.T + n - 1) / n + 15) / 16 * 16;
+    if (per <= kTokChunk) return 0;
+    Shape pass = sh, last = sh;
+    pass.T = sh.T < per ? sh.T : per;
+    last.T = sh.T - (sh.T - 1) / per * per;
+    if (wide_pass_fits(pass, g, form, head, bytes) &&
+        (last.T <= kTokChunk || wide_pass_fits(last, g, form, head, bytes)))
+      return per;
   }
-  return 0;
 }
 
 hipError_t launch_wide(const Shape& sh, Gate g, bool dense, const Form& form, const float* x, const void* lopa_a,
                        const void* gate_w, const void* w_up, const void* w_down_t, float t, void* base, size_t head,
-                       float* y, hipStream_t s) {
+                       size_t bytes, float* y, hipStream_t s) {
   WideLayout w;
-  wide_layout(sh.T, sh.d, sh.d_ff, g == Gate::LoPA ? sh.r : 0, form.g_idx != nullptr, base, head, &w);
+  if (wide_layout(sh.T, sh.d, sh.d_ff, g == Gate::LoPA ? sh.r : 0, form.g_idx != nullptr, base, head, &w) > bytes)
+    return hipErrorInvalidValue;  // not a pass of wide_pass_tokens
   return wide_format<kWTiles>(sh, g, dense, form, x, lopa_a, gate_w, w_up, w_down_t, t, w, y, s);
 }
 

@@ -105,3 +105,24 @@ def test_wide_without_a_workspace_argument(gu):
     ffn.ffn_sparse_forward_noalloc(dev.x, dev.w_gate, dev.w_up, dev.w_down_t, t, y)
     assert gu.rel_err(y.cpu().numpy(), gu.run_oracle(inp, t).y) <= 3e-5
     assert np.isfinite(y.cpu().numpy()).all()
+
+
+@pytest.mark.parametrize("shape", [(256, 8, 8198, 4136), (100, 264, 300, 800)],
+                         ids=["smaller pass, larger layout", "z in a region of its own"])
+def test_wide_stays_in_the_workspace(gu, shape):
+    """Ranks near and above d_ff / 2: z's partial copies do not fit where zval goes later.  Nothing
+    behind the workspace is written, and the tokens of both ends of a pass are right."""
+    import torch
+    from paper_2609_31975_amd import ffn
+    T, d, d_ff, r = shape
+    t, n, guard = 1.6, ffn.workspace_bytes(*shape), 8 << 20
+    inp = wl.make_inputs(606, T, d, d_ff, r=r, wdt=BF16)
+    dev = gu.DevInputs(inp)
+    buf = torch.full((n + guard,), 0xA5, dtype=torch.uint8, device="cuda")
+    buf[:n].zero_()
+    y = torch.full((T, d), float("nan"), device="cuda")
+    ffn.ffn_lopa_sparse_forward(dev.x, dev.lopa_a, dev.lopa_b, dev.w_up, dev.w_down_t, t, y, buf[:n])
+    assert bool((buf[n:] == 0xA5).all())
+    sel = [0, 15, T // 2 - 1, T // 2, T - 1]
+    res = gu.run_oracle(inp, t, x=inp.x[sel])
+    gu.check_parity(res, y.cpu().numpy()[sel], None, None, t, BF16, what=str(shape))
