@@ -346,6 +346,9 @@ __device__ __forceinline__ TokSrc token_source(bool pre, const float* x, const u
 // 16 nt + (lane & 15), elements 32 ks + 8 (lane >> 4) .. + 7, the lo plane (nks ntt 64
 // entries later) their lo parts; zero past the batch and past d.  F32 (fp32 weights): one plane
 // of the fp32 values, elements 16 ks + 4 (lane >> 4) .. + 3.
+// Values go into the workspace as arithmetic leaves them, without signalling NaNs (the conversions to
+// bf16 quiet theirs): one with kZTag's bits would look like a published z to a later call.
+__device__ __forceinline__ uint32_t quiet(uint32_t v) { return (v & 0x7FFFFFFFu) > 0x7F800000u ? v | 0x00400000u : v; }
 template <bool F32>
 __global__ __launch_bounds__(kBlock) void k_split_tokens(const float* __restrict__ x, int C, int T, int nks, int ntt,
                                                          uint4* __restrict__ xs) {
@@ -354,7 +357,9 @@ __global__ __launch_bounds__(kBlock) void k_split_tokens(const float* __restrict
   const int lane = i % kWave, fr = i / kWave, nt = fr % ntt, ks = fr / ntt;
   const int tok = 16 * nt + (lane & 15), c = 4 * ks + (lane >> 4);
   if constexpr (F32) {
-    xs[i] = tok < T && c < C ? reinterpret_cast<const uint4*>(x)[(size_t)tok * C + c] : make_uint4(0u, 0u, 0u, 0u);
+    uint4 v = tok < T && c < C ? reinterpret_cast<const uint4*>(x)[(size_t)tok * C + c] : make_uint4(0u, 0u, 0u, 0u);
+    v.x = quiet(v.x), v.y = quiet(v.y), v.z = quiet(v.z), v.w = quiet(v.w);
+    xs[i] = v;
     return;
   }
   float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};

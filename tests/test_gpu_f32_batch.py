@@ -48,3 +48,23 @@ def test_f32_batch_full_form(gu, T):
     y, idx, act, _ = gu.run_gpu_ex(gu.DevInputs(inp), t, form)
     res = gu.run_oracle(inp, t, form=form)
     gu.check_parity(res, y, idx, act, t, wl.F32, what=f"full form T={T}", act_value=form.act_value)
+
+
+@pytest.mark.parametrize("T", [17, 80])
+@pytest.mark.parametrize("wdt", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+def test_nan_tokens_leave_no_z_tag(gu, wdt, T):
+    """Tokens that hold the signalling NaN that tags a published z: a batch leaves no such word in the
+    workspace, where a later single-token LoPA call of a larger rank would take it for one."""
+    import numpy as np
+    import torch
+    from paper_2609_31975_amd import ffn
+    tag, d = 0x7FA5A5A5, 256
+    inp = wl.make_inputs(503, T, d, 8, wdt=wdt)
+    bits = np.full((T, d), tag, np.uint32)
+    if wdt == wl.BF16:
+        bits[:, 0::2] = 0xA5A50000  # the low half of a word of two bf16
+    inp.x = bits.view(np.float32)
+    dev = gu.DevInputs(inp)
+    ws = ffn.alloc_workspace(T, d, 8)
+    ffn.ffn_sparse_forward(dev.x, dev.w_gate, dev.w_up, dev.w_down_t, 1.0, torch.empty_like(dev.x), ws)
+    assert not bool((ws.view(torch.int32) == tag).any())
