@@ -1144,9 +1144,8 @@ __global__ __launch_bounds__(kQ4Threads) void k_gate_up_q4(FFN_GATE_UP_PARAMS) {
 // then go to y with one fp32 atomic per token and column (y was cleared by the gate kernel).
 constexpr int kDnSlots = 4096;  // most rows of one row chunk
 // LDS entries of the packed list: the rows, up to three pad entries a segment (at most kBlock
-// segments), and empty entries for the groups past the last one that the loop looks at
-constexpr int kDnPad = 4 * kParts;
-constexpr int kDnList = kDnSlots + 3 * kBlock + 32 * (kDnPad + 1);
+// segments), and empty entries to the end of the last group
+constexpr int kDnList = kDnSlots + 3 * kBlock + 32;
 
 template <int NT, class W = WBf16>
 struct DnCfg {
@@ -1179,19 +1178,22 @@ struct DnRows {
   int zq[2];                  // zval quads of the lane group: entries 4 g .. and 16 + 4 g .., -1 for none
 };
 
-// C: loaded chunks per row, ch: this lane's chunk
+// cv: the lane's chunk is one of the row's.  A group past the ngrp listed ones has no entries.
 template <int NT, class W>
-__device__ __forceinline__ DnRows<NT, W> dn_rows(int group, const int* s_row, const int* s_zq, int C, int ch) {
+__device__ __forceinline__ DnRows<NT, W> dn_rows(int group, int ngrp, const int* s_row, const int* s_zq, bool cv) {
   using K = DnCfg<NT, W>;
   const int lane = lane_id();
+  const bool has = group < ngrp, ok = cv && has;
+  const int g = has ? group : 0;
   DnRows<NT, W> a;
 #pragma unroll
   for (int i = 0; i < K::NI; ++i) {
-    const int v = s_row[32 * group + K::entry(i, lane)];
-    a.row[i] = ch < C ? v : -1;
+    const int v = s_row[32 * g + K::entry(i, lane)];
+    a.row[i] = ok ? v : -1;
   }
-  a.zq[0] = s_zq[8 * group + (lane >> 4)];
-  a.zq[1] = s_zq[8 * group + 4 + (lane >> 4)];
+  const int z0 = s_zq[8 * g + (lane >> 4)], z1 = s_zq[8 * g + 4 + (lane >> 4)];
+  a.zq[0] = has ? z0 : -1;
+  a.zq[1] = has ? z1 : -1;
   return a;
 }
 
@@ -1301,8 +1303,6 @@ __global__ __launch_bounds__(kBlock) void k_down_mfma(const int32_t* __restrict_
   constexpr int PART_U4 = kParts * K::DT * 2 * NT * kWave;
   constexpr int BIG_U4 = STAGE_U4 + IDX_U4 > PART_U4 ? STAGE_U4 + IDX_U4 : PART_U4;
   __shared__ uint4 s_big[BIG_U4];
-  __shared__ int s_wquads[kBlock / kWave];
-  __shared__ int s_cnt[kBlock], s_quad[kBlock];  // per segment of the chunk: entries, first quad
   __shared__ uint2 s_alive[K::F32 ? kBlock : 1];  // fp32 weights: a bit an entry whose row is read
   uint4* const s_stage = s_big;
   int* const s_row = reinterpret_cast<int*>(s_big + STAGE_U4);
@@ -1333,37 +1333,50 @@ __global__ __launch_bounds__(kBlock) void k_down_mfma(const int32_t* __restrict_
     }
   };
   int v0[SU];
-  const int c = tid < nsc ? seg_count[seg_lo + tid] : 0;
+  // Every wave scans all counts: lane l those of segments 4 l .. 4 l + 3, so that a segment's place
+  // in the list comes from a register of the wave that lists it and no wave waits for another (with a
+  // scan over the workgroup, two more barriers and 512 empty entries past the last group: LoPA
+  // r = 512 on the 8B shape, 4 tokens, int8 30.9 -> 30.4 us a call, int4 30.3 -> 29.8; bf16 70B shape,
+  // r = 1024, 8 tokens 130.8 -> 130.4).
+  const Buf cb = make_buf(seg_count + seg_lo, 4u * (uint32_t)nsc);
+  int c[kParts], first[kParts];  // entries of segment 4 lane + p, its first quad
+#pragma unroll
+  for (int p = 0; p < kParts; ++p) c[p] = ldb32(cb, kParts * lane + p < nsc ? 4u * (uint32_t)(kParts * lane + p) : kOOB);
   uint2 live = make_uint2(0u, 0u);
   if constexpr (K::F32)
     if (tid < nsc) live = alive[seg_lo + tid];
   fetch(v0, wave);
-  const int quads = wave_inclusive_scan((c + 3) >> 2);
-  if (lane == kWave - 1) s_wquads[wave] = quads;
-  __syncthreads();
-  int qbase = 0, nquad = 0;
+  int quads = 0;
 #pragma unroll
-  for (int w = 0; w < kBlock / kWave; ++w) {
-    const int v = s_wquads[w];
-    qbase += w < wave ? v : 0;
-    nquad += v;
+  for (int p = 0; p < kParts; ++p) {
+    first[p] = quads;
+    quads += (c[p] + 3) >> 2;
   }
-  nquad = uniform(nquad);
+  const int upto = wave_inclusive_scan(quads);
+  const int nquad = __builtin_amdgcn_readlane(upto, kWave - 1);
   const int ngrp = (nquad + 7) / 8;
-  s_cnt[tid] = c;
-  if constexpr (K::F32) s_alive[tid] = live;
-  s_quad[tid] = qbase + quads - ((c + 3) >> 2);
-  for (int o = 4 * nquad + tid; o < 32 * (ngrp + kDnPad); o += kBlock) {
+  int cw = c[0], fw = first[0];  // of the wave's segments: 4 lane + wave
+#pragma unroll
+  for (int p = 1; p < kParts; ++p) {
+    cw = wave == p ? c[p] : cw;
+    fw = wave == p ? first[p] : fw;
+  }
+  fw += upto - quads;
+  for (int o = 4 * nquad + tid; o < 32 * ngrp; o += kBlock) {
     s_row[o] = -1;
     if ((o & 3) == 0) s_zq[o >> 2] = -1;
   }
-  __syncthreads();
+  if constexpr (K::F32) {
+    s_alive[tid] = live;
+    __syncthreads();
+  }
   for (int s0 = wave;; s0 += kParts * SU) {
 #pragma unroll
     for (int u = 0; u < SU; ++u) {
       const int sg = s0 + u * kParts;
       if (sg < nsc) {
-        const int n = s_cnt[sg], o = 4 * s_quad[sg] + lane;
+        const int n = __builtin_amdgcn_readlane(cw, sg / kParts);
+        const int o = 4 * __builtin_amdgcn_readlane(fw, sg / kParts) + lane;
         if (lane < ((n + 3) & ~3)) {
           bool read = lane < n;
           if constexpr (K::F32) read = read && (((lane < 32 ? s_alive[sg].x : s_alive[sg].y) >> (lane & 31)) & 1u);
@@ -1393,17 +1406,17 @@ __global__ __launch_bounds__(kBlock) void k_down_mfma(const int32_t* __restrict_
     // group past the last one loads nothing and adds zeros), so no load sits on a conditional
     // path.
     DnFrags<NT, W> f0, f1;
-    DnRows<NT, W> a = dn_rows<NT, W>(phase, s_row, s_zq, C, ch);
+    DnRows<NT, W> a = dn_rows<NT, W>(phase, ngrp, s_row, s_zq, ch < C);
     dn_issue(f0, a, db, zb, C, ch, T, ntt);
-    a = dn_rows<NT, W>(phase + GS, s_row, s_zq, C, ch);
+    a = dn_rows<NT, W>(phase + GS, ngrp, s_row, s_zq, ch < C);
     for (int j = phase;; j += 2 * GS) {
       dn_issue(f1, a, db, zb, C, ch, T, ntt);
       issue_barrier();
-      a = dn_rows<NT, W>(j + 2 * GS, s_row, s_zq, C, ch);
+      a = dn_rows<NT, W>(j + 2 * GS, ngrp, s_row, s_zq, ch < C);
       dn_mma(f0, s_stage + wave * 32 * K::PITCH, acc);
       dn_issue(f0, a, db, zb, C, ch, T, ntt);
       issue_barrier();
-      a = dn_rows<NT, W>(j + 3 * GS, s_row, s_zq, C, ch);
+      a = dn_rows<NT, W>(j + 3 * GS, ngrp, s_row, s_zq, ch < C);
       dn_mma(f1, s_stage + wave * 32 * K::PITCH, acc);
       if (j + 2 * GS >= ngrp) break;
     }
