@@ -164,6 +164,9 @@ hipError_t launch_split_tokens(const Shape& sh, const float* x, const Workspace&
 // take the call), the workspace that a pass of sh.T tokens uses, and the pass.  Its regions start
 // `head` bytes into the workspace of `bytes`.
 constexpr int kWidePass = 512;
+constexpr int kWDnRows = 4096;  // most rows of a down workgroup's chunk
+constexpr int kWDnSegs = 128;   // most segments of it
+int wide_down_chunks(int units, int d_ff, int nseg);
 size_t wide_pass_bytes(const Shape& sh, Gate g, const Form& form, size_t head);
 int wide_pass_tokens(const Shape& sh, Gate g, const Form& form, size_t head, size_t bytes);
 hipError_t launch_wide(const Shape& sh, Gate g, bool dense, const Form& form, const float* x, const void* lopa_a,

@@ -37,8 +37,6 @@ constexpr int kWTiles = 8;                  // token tiles (of 16) of a block
 constexpr int kWRows = 128;                 // most rows of a segment
 constexpr int kZRows = 64;                  // rows of A of a workgroup
 constexpr int kWCols = 128;                 // columns of a down workgroup
-constexpr int kWDnRows = 4096;              // most rows of a down workgroup's chunk
-constexpr int kWDnSegs = 128;               // most segments of it
 constexpr int kWDnPad = 10;  // iterations past the last one that the down loop looks at
 constexpr int kWDnList = kWDnRows + 3 * kWDnSegs + 64 * (kWDnPad + 1);  // packed entries, see k_wide_down
 constexpr int kXcds = 8;
@@ -827,23 +825,36 @@ hipError_t wide_z(const Shape& sh, const Form& form, const float* x, const void*
   return hipGetLastError();
 }
 
+}  // namespace
+
+// Row chunks of the down grid (units of S column groups x token blocks, one workgroup a CU): chunks of
+// at least 512 rows (each adds T d fp32 atomics) and at most kWDnRows, kWDnSegs; of these counts the one
+// with the least rounds over the CUs times a workgroup's iterations and kWDnFixed more (its list, first
+// loads, sums and atomics).  A chunk too many costs a round: d 5120 (40 column groups), d_ff 15000, 33
+// tokens, 7 chunks 59.4 us, 6 40.7; d 3072, d_ff 15000, 64 tokens, 11 chunks 51.1, 10 31.7.
+constexpr int kWDnFixed = 8;
+int wide_down_chunks(int units, int d_ff, int nseg) {
+  const int rows = (d_ff + nseg - 1) / nseg;
+  int per = kWDnRows / rows;
+  if (per > kWDnSegs) per = kWDnSegs;
+  const int least = (nseg + per - 1) / per, most = (d_ff + 511) / 512;
+  int best = least;
+  int64_t cost = INT64_MAX;
+  for (int c = least; c == least || (c <= most && (int64_t)units * (c - 1) < 4 * kWCus); ++c) {
+    const int64_t rounds = ((int64_t)units * c + kWCus - 1) / kWCus, t = rounds * (64 * kWDnFixed + d_ff / c);
+    if (t < cost) cost = t, best = c;  // in rows, 64 an iteration
+  }
+  return best < nseg ? best : nseg;
+}
+
+namespace {
+
 template <class W, int NT>
 hipError_t wide_kernels(const Shape& sh, const WideArgs& a, const WideLayout& w, const void* w_down_t, hipStream_t s) {
   const int units = (w.nseg + kXcds - 1) / kXcds * kXcds;
   const hipError_t e = launch_gate_kernel_n(k_wide_gate_up<W, NT>, units * w.nb, kWThreads, s, a);
   if (e != hipSuccess) return e;
-  // Down grid: about one workgroup a CU, chunks of at least 512 rows (each chunk adds T d fp32
-  // atomics) and at most kWDnRows, kWDnSegs.
-  const int S = (sh.d + kWCols - 1) / kWCols;
-  int R = (kWCus + S * w.nb - 1) / (S * w.nb);
-  const int most = (sh.d_ff + 511) / 512;
-  if (R > most) R = most;
-  const int rows = (sh.d_ff + w.nseg - 1) / w.nseg;
-  int per = kWDnRows / rows;
-  if (per > kWDnSegs) per = kWDnSegs;
-  const int least = (w.nseg + per - 1) / per;
-  if (R < least) R = least;
-  if (R > w.nseg) R = w.nseg;
+  const int S = (sh.d + kWCols - 1) / kWCols, R = wide_down_chunks(S * w.nb, sh.d_ff, w.nseg);
   const int du = (S * R + kXcds - 1) / kXcds * kXcds;
   k_wide_down<W, NT><<<du * w.nb, kWThreads, 0, s>>>(w.seg_count, w.seg_idx, w.zf, w.nseg, w.qps, sh.d_ff, R, w.ntt, w.nb,
                                                  static_cast<const uint4*>(w_down_t), sh.d / W::EPC, sh.d, sh.T, a.y);

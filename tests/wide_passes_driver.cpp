@@ -1,5 +1,6 @@
 // Host check of the passes of calls of more than 64 tokens: whatever the call, the regions of every
-// pass that is launched lie inside the workspace that ffn_workspace_bytes asks for.
+// pass that is launched lie inside the workspace that ffn_workspace_bytes asks for, and the row chunks
+// of the down grid fit its workgroups' lists.
 // Prints "calls passes" and exits 0, or the first pass that does not fit and exits 1.
 #include <cstdio>
 #include <cstdint>
@@ -40,6 +41,15 @@ bool check(int wdt, int T, int d, int d_ff, int r, bool has_g, size_t extra) {
   return true;
 }
 
+// The row chunks of the down grid fit its workgroups' lists.
+bool check_chunks(int units, int d_ff, int nseg) {
+  const int R = ffn::wide_down_chunks(units, d_ff, nseg);
+  const int rows = (d_ff + nseg - 1) / nseg, segs = R > 0 ? (nseg + R - 1) / R : 0;
+  if (R >= 1 && R <= nseg && segs <= ffn::kWDnSegs && segs * rows <= ffn::kWDnRows) return true;
+  std::printf("%d chunks: %d units, d_ff %d, %d segments\n", R, units, d_ff, nseg);
+  return false;
+}
+
 uint64_t g_state = 88172645463325252ull;
 uint32_t next(uint32_t n) {  // 0 .. n - 1
   g_state ^= g_state << 13, g_state ^= g_state >> 7, g_state ^= g_state << 17;
@@ -55,6 +65,10 @@ int main() {
                           {508, 2112, 9510, 4792, 0},  {486, 5464, 15401, 7720, 1}};
   for (const auto& k : known)
     if (!check(1, k[0], k[1], k[2], k[3], k[4] != 0, 0)) return 1;
+  for (int i = 0; i < 20000; ++i) {
+    const int d_ff = 1 + (int)next(next(2) ? 1 << 20 : 30000), rows = next(2) ? 64 : 128;
+    if (!check_chunks(1 + (int)next(300), d_ff, (d_ff + rows - 1) / rows)) return 1;
+  }
   for (int i = 0; i < 400000; ++i) {
     const int wdt = 1 + (int)next(3), q = wdt == 1 ? 8 : wdt == 2 ? 16 : 32;
     const int d = q * (1 + (int)next(8192 / q)), d_ff = 1 + (int)next(next(2) ? 30000 : 2000);
