@@ -756,10 +756,6 @@ __global__ __launch_bounds__(kBlock) void k_split_z(const float* __restrict__ zp
 }
 
 // ------------------------------------------------------------------ host side
-// Rows a segment: 128, or 64 where segments of 128 would leave many compute units without a
-// workgroup (the product of half the rows re-reads the tokens twice as often).
-constexpr int kWFill = 192;
-
 struct WideLayout {
   int nseg, qps, ntt, nb;
   int zparts;    // partial copies of z there is room for
@@ -774,8 +770,12 @@ size_t wide_layout(int T, int d, int d_ff, int r, bool has_g, void* base, size_t
   WideLayout w{};
   w.ntt = (T + 15) / 16;
   w.nb = (w.ntt + kWTiles - 1) / kWTiles;
+  // Rows a segment: 64 where the workgroups of those (one a CU) take one round, else 128, whose product
+  // reads the tokens half as often.  bf16, standard gating, 128 -> 64 rows: d 4096, d_ff 11000, 100 tokens
+  // (172 workgroups of 64) 156 -> 135 us.  64 -> 128: 200 tokens (344) 224 -> 170, d 8192, d_ff 21000, 65
+  // tokens (329) 414 -> 345.
   const int big = (d_ff + kWRows - 1) / kWRows;
-  const int rows = (int64_t)big * w.nb < kWFill ? kWRows / 2 : kWRows;
+  const int rows = 2 * (int64_t)big * w.nb <= kWCus ? kWRows / 2 : kWRows;
   w.nseg = (d_ff + rows - 1) / rows;
   w.qps = ((d_ff + w.nseg - 1) / w.nseg + 3) / 4;
   size_t off = head;
