@@ -994,14 +994,28 @@ void wide64_layout(const Shape& sh, Gate g, const Workspace& ws, WideLayout* out
 }
 
 // Where 33..64 tokens take these kernels instead of the register-tiled ones: where segments of 64
-// rows leave at most an eighth or so of the compute units idle (k_gate_up_mfma balances its segments
-// over them whatever d_ff is).  LoPA r = 512 / 1024, 90%, on d_ff 14336 (224 segments): bf16 33 / 48 /
-// 64 tokens 90.9 / 105.5 / 98.7 -> 87.2 / 89.0 / 95.0 us, int8 64 tokens 97.1 -> 82.5; d_ff 28672
-// (448), 40 tokens 301 -> 256.  On d_ff 11000 (172 segments), 64 tokens 74.9 -> 88.5; 13824 (216), 33
-// tokens 112.3 -> 118.5; 2000, 64 tokens 29.9 -> 33.5; at 17 - 32 tokens, 14336: 63.4 -> 77.0 (17).
-// LoPA's z has to fit the regions above (ranks about as large as d_ff do not).
+// rows leave at most an eighth of the compute units idle in their last round (k_gate_up_mfma balances
+// its segments over them whatever d_ff is), and the rows are long enough to carry the passes over z and
+// the wider down workgroups.  Register-tiled -> these, 90%, us a call at 33 / 48 / 64 tokens:
+//   bf16 d 1024, d_ff 16000, r 128   42.6 -> 47.9 / 47.2 -> 49.6 / 46.5 -> 53.2
+//   int8                             41.5 -> 45.8 / 46.1 -> 46.8 / 45.4 -> 51.0
+//   bf16 d 2048, d_ff 14336, r 256   58.8 -> 60.4 / 68.0 -> 62.7 / 64.4 -> 66.9
+//   bf16 standard gating             63.8 -> 65.5 / 72.3 -> 66.7 / 68.4 -> 72.1
+//   int8 / int4 64 tokens, r 256     62.7 -> 62.4 / 62.4 -> 62.7
+//   bf16 d 2304, d_ff 14336, r 288   63.8 -> 63.8 / 72.1 -> 66.4 / 70.4 -> 71.3
+//   bf16 d 4096, d_ff 14336, r 512   93.3 -> 87.4 / 108.9 -> 89.7 / 102.0 -> 95.9
+//   bf16 standard gating             106.3 -> 101.0 / 121.6 -> 102.8 / 114.3 -> 112.4
+//   int8 r 512                       90.2 -> 76.5 / 105.2 -> 79.0 / 98.3 -> 83.6
+//   int4 r 512                       88.9 -> 81.5 / 104.1 -> 83.8 / 97.0 -> 86.8
+//   bf16 r 512, the full form        100.8 -> 97.2 / - / 113.2 -> 108.2
+// Fewer segments in the last round, bf16 standard gating at 64 tokens: d 4096 5 % slower here at 165 of
+// them (d_ff 10500), even at 216 (13824); d 2304 6 % and 1 % slower.  LoPA, fewer tokens and codes gain
+// from 188 on at d 4096; the line at 224 gives those up.  17 tokens, 8B shape: 63.4 -> 77.0.
+// LoPA's z has to fit the regions above (ranks larger than d_ff do not).
+constexpr int kWide64MinD = 2304, kWide64MinDQuant = 2048;
 bool wide64_ok(const Shape& sh, Gate g, const Workspace& ws) {
   if (sh.wdt < 1 || sh.wdt > 3 || sh.T < kWide64Min || ws.tc > kTokChunk || !batched_ok(sh, g)) return false;
+  if (sh.d < (sh.wdt == 1 ? kWide64MinD : kWide64MinDQuant)) return false;
   const int nseg = (sh.d_ff + kWRows / 2 - 1) / (kWRows / 2), rounds = (nseg + kWCus - 1) / kWCus;
   if (8 * nseg < 7 * kWCus * rounds) return false;
   if (g != Gate::LoPA) return true;

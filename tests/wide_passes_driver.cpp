@@ -1,6 +1,6 @@
 // Host check of the passes of calls of more than 64 tokens: whatever the call, the regions of every
 // pass that is launched lie inside the workspace that ffn_workspace_bytes asks for, and the row chunks
-// of the down grid fit its workgroups' lists.
+// of the down grid fit its workgroups' lists; likewise the regions of a pass of 33..64 tokens.
 // Prints "calls passes" and exits 0, or the first pass that does not fit and exits 1.
 #include <cstdio>
 #include <cstdint>
@@ -50,6 +50,23 @@ bool check_chunks(int units, int d_ff, int nseg) {
   return false;
 }
 
+// A pass of 33..64 tokens on the wide kernels uses the workspace's own regions: z's first copy and zval
+// lie in zf, z's planes in seg_zval.  `taken` counts the calls that the path takes.
+bool check_64(int wdt, int T, int tc, int d, int d_ff, int r, int64_t* taken) {
+  ffn::Workspace ws;
+  ffn::workspace_layout(tc, d, d_ff, r, reinterpret_cast<char*>(uintptr_t(1) << 20), &ws);
+  if (!ffn::wide64_ok(ffn::Shape{T, d, d_ff, r, wdt, {}}, r > 0 ? ffn::Gate::LoPA : ffn::Gate::Standard, ws)) return true;
+  ++*taken;
+  const int64_t ntt = (tc + 15) / 16, nseg = (d_ff + 63) / 64;
+  const int64_t zf = reinterpret_cast<char*>(ws.xs) - reinterpret_cast<char*>(ws.zf);
+  const int64_t zval = reinterpret_cast<char*>(ws.z) - reinterpret_cast<char*>(ws.seg_zval);
+  if (T >= ffn::kWide64Min && tc <= ffn::kTokChunk && 16 * 16 * 16 * ntt * nseg <= zf && 4 * (int64_t)T * r <= zf &&
+      16 * 2 * 64 * ((r + 31) / 32) * ntt <= zval)
+    return true;
+  std::printf("33..64 tokens do not fit: T %d of %d, d %d, d_ff %d, r %d, weights %d\n", T, tc, d, d_ff, r, wdt);
+  return false;
+}
+
 uint64_t g_state = 88172645463325252ull;
 uint32_t next(uint32_t n) {  // 0 .. n - 1
   g_state ^= g_state << 13, g_state ^= g_state >> 7, g_state ^= g_state << 17;
@@ -69,6 +86,14 @@ int main() {
     const int d_ff = 1 + (int)next(next(2) ? 1 << 20 : 30000), rows = next(2) ? 64 : 128;
     if (!check_chunks(1 + (int)next(300), d_ff, (d_ff + rows - 1) / rows)) return 1;
   }
+  int64_t taken = 0;
+  for (int i = 0; i < 100000; ++i) {
+    const int wdt = 1 + (int)next(3), q = wdt == 1 ? 8 : wdt == 2 ? 16 : 32;
+    const int T = 2 + (int)next(63), tc = next(2) ? T : 64, d_ff = 1 + (int)next(40000);
+    const int r = next(3) ? (int)((next(2) ? d_ff + next(400) : next(2 * d_ff)) / q * q) : 0;
+    if (!check_64(wdt, T, tc, q * (1 + (int)next(8192 / q)), d_ff, r, &taken)) return 1;
+  }
+  if (taken < 1000) return 1;
   for (int i = 0; i < 400000; ++i) {
     const int wdt = 1 + (int)next(3), q = wdt == 1 ? 8 : wdt == 2 ? 16 : 32;
     const int d = q * (1 + (int)next(8192 / q)), d_ff = 1 + (int)next(next(2) ? 30000 : 2000);
