@@ -772,7 +772,7 @@ size_t wide_layout(int T, int d, int d_ff, int r, bool has_g, void* base, size_t
   w.nb = (w.ntt + kWTiles - 1) / kWTiles;
   // Rows a segment: 64 where the workgroups of those (one a CU) take one round, else 128, whose product
   // reads the tokens half as often.  bf16, standard gating, 128 -> 64 rows: d 4096, d_ff 11000, 100 tokens
-  // (172 workgroups of 64) 156 -> 135 us.  64 -> 128: 200 tokens (344) 224 -> 170, d 8192, d_ff 21000, 65
+  // (172 workgroups of 64) 156 -> 135 us.  64 -> 128: 200 tokens (344) 225 -> 170, d 8192, d_ff 21000, 65
   // tokens (329) 414 -> 345.
   const int big = (d_ff + kWRows - 1) / kWRows;
   const int rows = 2 * (int64_t)big * w.nb <= kWCus ? kWRows / 2 : kWRows;
@@ -933,6 +933,27 @@ bool wide_pass_fits(const Shape& sh, Gate g, const Form& form, size_t head, size
          256 * (int64_t)w.nseg * w.qps * kWTiles < lim && 4 * (int64_t)sh.T * sh.d < lim / 4 &&
          4 * (int64_t)sh.T * (r > 0 ? r : 1) < lim / 4;
 }
+
+// Passes of 64 against one pass here, 90%: 8B shape LoPA r = 512, 65 / 96 / 128 / 200 / 256 tokens
+// 119.2 / 174.2 / 203.2 / 351.9 / 405.8 -> 108.1 / 116.8 / 126.7 / 162.7 / 170.6 us; d 512, d_ff 2000, 100
+// tokens 55.9 -> 36.5; 70B shape LoPA r = 1024, 100 tokens 640.8 -> 319.9.
+// A few tokens past 64 leave a second pass little to do, and 64 and the rest is then the cheaper way where
+// this path's latency counts.  One pass / 64 and the rest, us a call:
+//   one token over (the single-token kernels take it), bf16 LoPA d 128, d_ff 400 37.3 / 30.7, d 512,
+//   d_ff 1500 41.6 / 42.4; standard gating d 256, d_ff 700 30.3 / 28.5, d 384, d_ff 1200 34.8 / 35.6;
+//   one over long rows of few neurons, standard gating, d 4096: int4 d_ff 9000 115.0 / 105.7, 13000
+//   122.3 / 120.9; int8 9000 111.1 / 106.9, 11000 115.1 / 115.9; bf16 5000 103.0 / 99.3, 7000 107.3 / 106.6;
+//   LoPA, 72 tokens: int4 d 128, d_ff 400 39.4 / 36.1, d 384, d_ff 1152 45.1 / 43.5; int8 39.0 / 36.7, 44.3 /
+//   44.7; bf16 d 32, d_ff 1000 6 % slower in one pass, d 256, d_ff 700 38.0 / 39.6.
+bool rest_is_cheap(const Shape& sh, Gate g) {
+  const int64_t n = (int64_t)sh.d * sh.d_ff;
+  const bool lopa = g == Gate::LoPA, codes = sh.wdt != 1;
+  if (sh.T == kTokChunk + 1 && n <= (lopa ? 1500000 : 640000)) return true;
+  if (sh.T == kTokChunk + 1 && !lopa && sh.d >= 2048 && sh.d_ff <= (sh.wdt == 3 ? 12288 : sh.wdt == 2 ? 9216 : 6144))
+    return true;
+  if (!lopa) return false;
+  return sh.T <= (codes && n <= 130000 ? 96 : 80) && n <= (codes ? 475000 : 130000);
+}
 }  // namespace
 
 // Tokens of the passes of a call of sh.T: as few equal passes (in whole token tiles, of at most
@@ -941,12 +962,8 @@ bool wide_pass_fits(const Shape& sh, Gate g, const Form& form, size_t head, size
 // last pass of fewer tokens than the others is checked by itself: a layout need not shrink with its
 // tokens (fewer blocks can mean smaller segments and so fewer zval quads, and z's copies then a
 // region of their own).
-// Passes of 64 against one pass here, 90%: 8B shape LoPA r = 512, 65 / 96 / 128 / 200 / 256 tokens
-// 118.8 / 171.7 / 199.5 / 345.6 / 398.6 -> 110.5 / 117.9 / 124.0 / 158.6 / 167.2 us; d 512, d_ff 2000,
-// 100 tokens 51.8 -> 37.8; 70B shape LoPA r = 1024, 100 tokens 639.8 -> 329.1.  65 tokens is the
-// smallest call that would need two passes of 64.
 int wide_pass_tokens(const Shape& sh, Gate g, const Form& form, size_t head, size_t bytes) {
-  if (sh.wdt < 1 || sh.wdt > 3 || sh.T <= kTokChunk) return 0;
+  if (sh.wdt < 1 || sh.wdt > 3 || sh.T <= kTokChunk || rest_is_cheap(sh, g)) return 0;
   Shape one = sh;
   one.T = kTokChunk;
   if (!batched_ok(one, g)) return 0;

@@ -20,8 +20,13 @@ def gu():
 
 # T, d, d_ff, r, wdt, threshold
 SHAPES = [
-    (65, 8, 3, 0, BF16, 0.0),           # one chunk, one segment of three rows, a tile of one token
-    (66, 72, 130, 8, BF16, 0.3),        # segments of 43 rows, a k step of one chunk, a rank of one
+    (65, 8, 3, 0, BF16, 0.0),           # 64 tokens, then one on the single-token kernels
+    (66, 72, 130, 8, BF16, 0.3),        # 64 tokens, then two
+    (81, 8, 3, 0, BF16, 0.0),           # one chunk, one segment of three rows, a tile of one token
+    (97, 72, 130, 8, BF16, 0.3),        # segments of 43 rows, a k step of one chunk, a rank of one
+    (65, 264, 2500, 0, BF16, 1.6),      # one token past 64 on the wide kernels
+    (65, 2048, 300, 0, I4, 1.6),        # ... and not: long rows of codes, few neurons
+    (96, 64, 300, 64, I8, 1.6),         # LoPA with codes on a small layer: 64 tokens, then 32
     (80, 264, 1000, 40, BF16, 1.6),
     (80, 136, 1000, 0, BF16, 3.0),      # small unions, some segments with none
     (100, 1032, 999, 72, BF16, 1.6),    # an odd d_ff; 129 chunks a row; nine column groups
