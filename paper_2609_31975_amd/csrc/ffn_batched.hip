@@ -732,7 +732,7 @@ __device__ __forceinline__ void gate_up_body(const float* __restrict__ x, const 
 // whose fragments carry both partial copies of z).
 template <class W, bool LOPA, bool DENSE, int NT, int FORM>
 __global__ __launch_bounds__(kBlock) void k_gate_up_mfma(FFN_GATE_UP_PARAMS) {
-  constexpr int KU = NT == 1 ? (LOPA && !is_f32<W>() ? 2 : 4) : (LOPA && NT == 4 && !is_f32<W>() ? 1 : 2);
+  constexpr int KU = NT == 1 ? (LOPA ? 2 : 4) : (LOPA && NT == 4 && !is_f32<W>() ? 1 : 2);
   gate_up_body<W, LOPA, DENSE, NT, KU, NT == 1 ? 4 : 2, FORM>(FFN_GATE_UP_ARGS);
 }
 
@@ -1535,13 +1535,16 @@ hipError_t gate_mfma(const Shape& sh, const Form& form, const float* x, const vo
   const int grid = two ? kSegGrid2 : kSegGrid;
   ws.nseg = segments_for(sh.d_ff, grid);
   const int g = ws.nseg < grid ? ws.nseg : grid;
-  auto kernel = k_gate_up_mfma<W, LOPA, DENSE, NT, FORM>;
-  if constexpr (NT == 1)
-    if (two) kernel = k_gate_up_mfma2<W, LOPA, DENSE, FORM>;
-  return launch_gate_kernel(kernel, g, s, x, (const float*)ws.z, static_cast<const uint4*>(gate_w), Cg,
+  auto launch = [&](auto kernel) {
+    return launch_gate_kernel(kernel, g, s, x, (const float*)ws.z, static_cast<const uint4*>(gate_w), Cg,
                             static_cast<const uint4*>(w_up), Cu, sh.T, sh.d, sh.d_ff, ws.nseg, t, ws.slots, ws.tc,
                             ws.meta, ws.seg_count, ws.seg_idx, ws.seg_act, ws.zf, y, ws.xs, token_tiles(ws), form,
                             (const float*)ws.gx, LOPA ? sh.sc.b : sh.sc.gate, sh.sc.up, sh.sc.down, alive_masks(ws), seg_quads(sh.d_ff, ws.nseg));
+  };
+  if constexpr (NT == 1)
+    if (two) return launch(k_gate_up_mfma2<W, LOPA, DENSE, FORM>);
+  if constexpr (NT > 1 || !is_f32<W>()) return launch(k_gate_up_mfma<W, LOPA, DENSE, NT, FORM>);
+  return hipErrorInvalidValue;  // one tile of fp32 rows: `two` holds
 }
 
 template <class W, bool LOPA, bool DENSE, int FORM>
