@@ -11,7 +11,7 @@ namespace ffn {
 constexpr int kWave = 64;
 constexpr int kSegMax = 64;       // most gate rows per segment (one 64-lane ballot)
 constexpr int kSegGeneric = 32;   // rows per segment of the element-wise kernels
-constexpr int kBlock = 256;       // threads per workgroup for every kernel
+constexpr int kBlock = 256;       // threads per workgroup, where a kernel does not state its own
 constexpr int kTokChunk = 64;     // tokens per pass; a larger batch runs as several passes
 constexpr int kListWindow = 1024; // active entries staged in LDS at a time by the down kernel
 constexpr int kPreSplitMin = 17;  // batches of more than one 16-token tile get their tokens pre-split

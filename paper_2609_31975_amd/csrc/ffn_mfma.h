@@ -23,7 +23,7 @@ __device__ __forceinline__ bf16x8_t bf8(uint4 v) { return __builtin_bit_cast(bf1
 // the other, so a long range in one accumulator rounds like a serial sum (a call's error against
 // 64 bits at d = 3840, d_ff = 14231, r = 480, 16 tokens: 7.9e-7, the vector-ALU kernels' 3.5e-7).
 // Every k step of the gate and W_up products is summed from zero, then into its load group's
-// sum, then into the running sum; the down product sums every group of 32 rows from zero (3.4e-7).
+// sum, then into the running sum; the down product sums every group of 32 rows from zero (3.1e-7).
 template <class W>
 constexpr bool is_f32() {
   return W::EPC == 4;
