@@ -680,7 +680,7 @@ __global__ __launch_bounds__(kBlock) void k_lopa_z_row(const float* __restrict__
 // clears the tags.  A workgroup that has not seen every component after form.z_wait ticks
 // (kZWaitTicks unless a test shortens it) computes the missing ones itself, so the kernel
 // finishes whatever the residency of its workgroups.
-template <class W, bool LOPA, bool DENSE, int CPLG, int CPLU, int FORM, int CPLA = 0>
+template <class W, bool LOPA, bool DENSE, int CPLG, int CPLU, int FORM, int CPLA = 0, bool XL = true>
 __global__ __launch_bounds__(kBlock) void k_gate_up_t1(const float* __restrict__ x, const float* __restrict__ z,
                                                        const uint4* __restrict__ gate_w, int Cg, int lprg,
                                                        int lprg_log2, const uint4* __restrict__ w_up, int Cu,
@@ -737,9 +737,8 @@ __global__ __launch_bounds__(kBlock) void k_gate_up_t1(const float* __restrict__
     // thread a share, ahead of the gate stream, and staged in LDS during the compaction, so
     // that the W_up rows go out right after it (every wave reading 16 KB of x there had put
     // 50 MB of L2 reads in front of the 12 MB of W_up rows).  Rows of more than 8 chunks a lane
-    // likewise: fp32 d 3840, d_ff 14231, r 480 24.6 -> 23.6 us a call, bf16 d 8192, d_ff 28672, r 1024
-    // 38.2 -> 37.0
-    constexpr bool kXLds = !limb_vec<W, CPLU>() && !DENSE;
+    // likewise where XL says so (see long_rows_xl)
+    constexpr bool kXLds = !limb_vec<W, CPLU>() && !DENSE && XL;
     constexpr int XF4 = W::EPC / 4, kXF4 = kXLds ? CPLU * kWave * XF4 : kBlock, kXPT = kXF4 / kBlock;
     static_assert(kXPT * kBlock == kXF4, "x shares");
     __shared__ float4 s_xu[kXLds ? kXF4 : 1];
@@ -1758,12 +1757,12 @@ bool fast_ok(const Shape& sh, Gate g) {
   return true;
 }
 
-template <class W, bool LOPA, bool DENSE, int FORM, int CPLG, int CPLU, int CPLA = 0>
+template <class W, bool LOPA, bool DENSE, int FORM, int CPLG, int CPLU, int CPLA = 0, bool XL = true>
 hipError_t go_gate_up_t1(const Shape& sh, const Form& form, const float* x, const void* gate_w, const void* w_up,
                          float t, Workspace& ws, float* y, hipStream_t s, const void* lopa_a = nullptr) {
   const int Cu = sh.d / W::EPC, Cg = LOPA ? sh.r / W::EPC : Cu;
   const int lpru = lanes_per_row(Cu, CPLU), lprg = lanes_per_row(Cg, CPLG);
-  auto kernel = k_gate_up_t1<W, LOPA, DENSE, CPLG, CPLU, FORM, CPLA>;
+  auto kernel = k_gate_up_t1<W, LOPA, DENSE, CPLG, CPLU, FORM, CPLA, XL>;
   static int per_cu = 0;  // one cache per instantiation
   ws.nseg = resident_segments(kernel, &per_cu, sh.d_ff);
   return launch_gate_kernel(kernel, ws.nseg, s, x, (const float*)ws.z, static_cast<const uint4*>(gate_w), Cg, lprg,
@@ -1785,6 +1784,19 @@ bool fuses_z(const Shape& sh) {
   }
 }
 
+// Whether rows of more than 8 chunks a lane take x for the W_up dots from LDS (the gate kernel's XL).
+// Staging it costs 32 registers and 32 KB across the gate stream: it wins where that stream leaves room
+// (B rows of one chunk a lane, or well into the second), and loses where it does not.  From memory ->
+// from LDS, 90%, us a call: bf16 d 5120, d_ff 16896, r 320 (40 chunks) 23.6 -> 22.0, d_ff 13824, r 640
+// (80) 20.1 -> 20.9, d_ff 16896, r 1136 (142) 28.3 -> 27.4; d 8192, d_ff 27033, r 1024 36.7 -> 35.5; r past
+// 4096, where the B rows take 16 chunks a lane too, d 5120, d_ff 18432, r 4104 52.3 -> 73.9; fp32 d 3840, d_ff
+// 14592, r 480 (120) 24.9 -> 23.9, d_ff 10368, r 848 (212) 26.2 -> 26.6, d 3584, d_ff 9676, r 792 23.8 -> 24.8.
+template <class W>
+bool long_rows_xl(const Shape& sh) {
+  const int cu = sh.d / W::EPC, cg = sh.r / W::EPC;
+  return W::EPC == 4 ? cg <= 2 * kWave : cg <= kWave || cg > 90 || cu > 800;
+}
+
 template <class W, bool LOPA, bool DENSE, int FORM>
 hipError_t gate_up_fast(const Shape& sh, const Form& f, const float* x, const void* gate_w, const void* w_up, float t,
                         Workspace& ws, float* y, hipStream_t s, const void* lopa_a) {
@@ -1798,13 +1810,17 @@ hipError_t gate_up_fast(const Shape& sh, const Form& f, const float* x, const vo
       if (lopa_a && fuses_z<W>(sh)) {
         if (cplu == L)
           return go_gate_up_t1<W, true, DENSE, FORM, L, L, 2>(sh, f, x, gate_w, w_up, t, ws, y, s, lopa_a);
+        if constexpr (!DENSE)
+          if (!long_rows_xl<W>(sh))
+            return go_gate_up_t1<W, true, DENSE, FORM, L, H, 4, false>(sh, f, x, gate_w, w_up, t, ws, y, s, lopa_a);
         return go_gate_up_t1<W, true, DENSE, FORM, L, H, 4>(sh, f, x, gate_w, w_up, t, ws, y, s, lopa_a);
       }
     }
     if (cplg == L && cplu == L) return go_gate_up_t1<W, true, DENSE, FORM, L, L>(sh, f, x, gate_w, w_up, t, ws, y, s);
     if (cplg == L && cplu == H) return go_gate_up_t1<W, true, DENSE, FORM, L, H>(sh, f, x, gate_w, w_up, t, ws, y, s);
     if (cplg == H && cplu == L) return go_gate_up_t1<W, true, DENSE, FORM, H, L>(sh, f, x, gate_w, w_up, t, ws, y, s);
-    return go_gate_up_t1<W, true, DENSE, FORM, H, H>(sh, f, x, gate_w, w_up, t, ws, y, s);
+    // bf16 rows of both products at 16 chunks a lane: x from memory (long_rows_xl)
+    return go_gate_up_t1<W, true, DENSE, FORM, H, H, 0, W::EPC != 8>(sh, f, x, gate_w, w_up, t, ws, y, s);
   } else {
     if (cplu == L) return go_gate_up_t1<W, false, DENSE, FORM, L, L>(sh, f, x, gate_w, w_up, t, ws, y, s);
     return go_gate_up_t1<W, false, DENSE, FORM, H, H>(sh, f, x, gate_w, w_up, t, ws, y, s);
