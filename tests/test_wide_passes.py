@@ -1,13 +1,17 @@
 """The passes of calls of more than 64 tokens stay inside the workspace: the library's own host
 arithmetic, swept on the CPU by a small driver linked to it."""
 import os
+import shutil
 import subprocess
+
+import pytest
 
 from paper_2609_31975_amd import build, ffn
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 def test_every_pass_fits_the_workspace(tmp_path):
     ffn.lib()
     exe = str(tmp_path / "wide_passes")
